@@ -26,8 +26,8 @@
  * Conventions for every entry point
  *   - All array pointers are DEVICE pointers (HBM), except where a name ends
  *     in _host.  The caller owns every buffer; the library allocates nothing.
- *     Its only state between calls is a process-wide counter that tags each
- *     call's use of the workspace (it never changes a result).  Calls on
+ *     Its only state between calls is a process-wide tag of the workspaces'
+ *     arrival counters (it never changes a result).  Calls on
  *     different streams may overlap as long as their output and workspace
  *     buffers do not.
  *   - Work is enqueued on `stream` (NULL = the null stream) and the call
@@ -178,8 +178,8 @@ int paged_attn_varlen(const void *q, const void *k_pages, const void *v_pages,
  *     chunk rows that take the per-row split-K kernel (fp32, head_dim 64)
  *     need rows x H_q x splits x (D + 2) x 4 bytes.
  *   - Every call on one GPU shares that GPU's array and leaves its contents
- *     behind (the arrival counters are tagged per call, so nothing needs
- *     clearing): calls that overlap in time on one GPU (other streams,
+ *     behind (a counter is left ready for the next call, and anything else in
+ *     its place is recognised, so nothing needs clearing): calls that overlap in time on one GPU (other streams,
  *     other threads) race on it and must be serialised by the caller.
  *   - Decode-only callers pass query_start_loc = {0, 1, ..., num_seqs} with
  *     num_q_rows = num_seqs and max_q_len = 1, which runs exactly the kernels

@@ -1,7 +1,7 @@
 // C ABI of libpagedattn.so: host-side validation, launch planning and
 // dispatch.  Validation runs before any HIP call, so a rejected call enqueues
 // nothing and is testable without a GPU.  The library allocates nothing; its
-// only state between calls is the counter that tags each call's range flags.
+// only state between calls is the tag of the workspaces' arrival counters.
 #include <climits>
 #include <math.h>
 #include <stddef.h>
@@ -106,7 +106,11 @@ int plan(const pa_dims_t* d, bool varlen, Plan* p) {
     p->st_cum = align256((size_t)pa::kStreamMaxGrid * p->W * sizeof(unsigned long long));
   }
   // chunked-prefill rows of a varlen call: MFMA kernel (bf16, head_dim 128)
-  p->prefill = varlen && p->stream && pa::prefill_supported(d->dtype, d->head_dim, s);
+  // (a call with at most one row per sequence has none; its decode rows then
+  // take the stream kernel alone, as paged_attn's do, instead of sharing the
+  // mixed launch with workgroups that would find no chunk)
+  p->prefill = varlen && p->stream && (d->max_q_len > 1 || rows > d->num_seqs) &&
+               pa::prefill_supported(d->dtype, d->head_dim, s);
   // split-K for whatever the stream and prefill paths do not take: in a
   // varlen call, chunk rows the MFMA kernel cannot take (there are none when
   // max_q_len <= 1: every row is then a decode row, which the stream kernel
@@ -131,16 +135,19 @@ int plan(const pa_dims_t* d, bool varlen, Plan* p) {
   return PA_OK;
 }
 
-// Tag of one call's arrival counters in the workspace: process-wide, never 0
-// and never repeated, so counters left in a reused workspace by earlier calls
-// (or found in a fresh one) do not match.  This counter is the library's only
-// state besides the fixed scratch below; it does not influence any result.
-unsigned long long next_token() {
-  static std::atomic<unsigned long long> counter{
-      0x9e3779b97f4a7c15ull ^
-      (unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count()};
-  unsigned long long t = counter.fetch_add(1, std::memory_order_relaxed) + 1;
-  return t != 0 ? t : counter.fetch_add(1, std::memory_order_relaxed) + 1;
+// Tag of the arrival counters in workspaces: 48 bits drawn once per process (a
+// mixed clock reading, never 0), so that what a fresh workspace holds does not
+// look like a counter.  It does not influence any result.
+unsigned long long counter_tag() {
+  static const unsigned long long tag = [] {
+    unsigned long long x = (unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count() ^
+                           (unsigned long long)std::chrono::system_clock::now().time_since_epoch().count() << 20;
+    x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
+    x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
+    x = (x ^ (x >> 31)) & ~0xffffull;
+    return x != 0 ? x : 0x9e3779b97f4a0000ull;
+  }();
+  return tag;
 }
 
 // Fixed device scratch of paged_attn_varlen_noalloc: the workspace of a call
@@ -260,7 +267,7 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
     sa.ws_o = reinterpret_cast<float*>(ws);
     sa.ws_ml = reinterpret_cast<float*>(ws + p.st_o);
     sa.ws_flag = reinterpret_cast<unsigned long long*>(ws + p.st_o + p.st_ml);
-    sa.token = next_token();
+    sa.tag = counter_tag();
     sa.bt_stride = dims->max_pages_per_seq;
     sa.scale_log2 = scale * 1.4426950408889634f;
     sa.B = dims->num_seqs;

@@ -86,9 +86,10 @@ template <int OFF> __device__ __forceinline__ float xor_lanes(float v) {
 
 // Partial records of the stream-K kernel are exchanged between workgroups of
 // one launch that may sit on different XCDs, whose L2 caches are not coherent
-// with each other.  They are written and read with device-scope relaxed
-// atomics (coherent at the device level, no L2 writeback or invalidate of the
-// whole cache), 8 bytes at a time.
+// with each other.  They are written and read with device scope (coherent at
+// the device level, no L2 writeback or invalidate of the whole cache): the
+// (m, l) pairs as relaxed 8-byte atomics, the outputs as 16-byte accesses with
+// the same cache bits.
 __device__ __forceinline__ void store_dev(float* p, float a, float b) {
   const unsigned long long v = (unsigned long long)__float_as_uint(a) | (unsigned long long)__float_as_uint(b) << 32;
   __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -99,9 +100,17 @@ __device__ __forceinline__ void load_dev2(const float* p, float& a, float& b) {
   a = __uint_as_float((uint32_t)v);
   b = __uint_as_float((uint32_t)(v >> 32));
 }
-__device__ __forceinline__ float load_dev(const float* p) {
-  return __uint_as_float(__hip_atomic_load(reinterpret_cast<const unsigned int*>(p), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT));
+typedef float f32x4_dev_t __attribute__((ext_vector_type(4)));
+constexpr int kDeviceScope = 16;  // sc1
+// Descriptor of one record of n floats (wave-uniform base).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t record_rsrc(const float* base, int n) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), (short)0, n * 4, 0x00020000);
+}
+__device__ __forceinline__ void store_dev4(__amdgpu_buffer_rsrc_t r, int i, f32x4_dev_t v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, i * 4, 0, kDeviceScope);
+}
+__device__ __forceinline__ f32x4_dev_t load_dev4(__amdgpu_buffer_rsrc_t r, int i) {
+  return __builtin_bit_cast(f32x4_dev_t, __builtin_amdgcn_raw_buffer_load_b128(r, i * 4, 0, kDeviceScope));
 }
 
 // Lazy rebasing of the online softmax (matrix-core paths): a row's running

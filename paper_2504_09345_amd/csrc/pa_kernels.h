@@ -61,8 +61,8 @@ struct StreamArgs {
   void* out;
   float* ws_o;       // [G][2][W][s][D] partial outputs (slot 0 head, 1 tail)
   float* ws_ml;      // [G][2][W][s][2]
-  unsigned long long* ws_flag;  // [G][W] arrival counters of cut items, keyed by the item's first range
-  unsigned long long token;     // tag of this call (never 0; differs from every earlier call's)
+  unsigned long long* ws_flag;  // [G][W] arrival counters of cut items (the first of each range's W)
+  unsigned long long tag;       // upper 48 bits of the counters (the process's; lower 16 bits 0)
   int64_t bt_stride;
   float scale_log2;
   int B, H_q, H_kv, max_context_len;

@@ -19,65 +19,113 @@ __device__ __forceinline__ bool info_end(int i) { return (i >> 6) & 1; }
 __device__ __forceinline__ int info_hb(int i) { return (i >> 7) & 63; }
 __device__ __forceinline__ int info_row(int i) { return (int)((unsigned)i >> 13); }
 
-// Merge the partial records of item (row r, KV head g) held by ranges
-// wg_first .. wg_last (record slot 1 of wg_first, slot 0 of the others; empty
-// ranges wrote nothing) and write the output row: one wave, E elements per
-// lane, records merged in range order.  Every part of the item stores its
-// record before it counts its arrival, and whichever part arrives last runs
-// this merge over all the records, so the result does not depend on which
-// range merges.  When a lane's E elements lie in one head (D a multiple of
-// E), the lane keeps only that head's running (M, L); the arithmetic of each
-// element is the same either way.
-template <typename T, int D, int S, int W>
-__device__ __forceinline__ void merge_item(const StreamArgs& a, int64_t U, int64_t G, int64_t wg_first,
-                                           int64_t wg_last, int w, int lane, T* out) {
-  constexpr int E = S * D / 64;  // elements per lane
-  constexpr bool kOneHead = D % E == 0;
-  constexpr int NH = kOneHead ? 1 : S;  // heads whose (M, L) the lane keeps
-  const int h0 = kOneHead ? lane * E / D : 0;
-  float M[NH], L[NH], acc[E];
+// Merge n <= 64 partial records of an item, those of ranges xs, xs + step, ...
+// (record slot 1 of the item's first range x0, slot 0 of the others), in range
+// order, by one wave; lane l takes the records' 16-byte chunks l, l + 64, ...
+// (Rec: a chunk's head and dims).  final: normalise and write the output row;
+// otherwise write the merged record over the first one's.  Every record is
+// stored before its part counts its arrival, and whichever part arrives last
+// merges all of them, so the result does not depend on which one it is.
+//
+// The merge is a chain of memory round trips (1 to 2 us each: the records
+// bypass the L2, which is not coherent between XCDs), so the (m, l) of all
+// records, record i by lane i, are loaded with the first kBatch records'
+// outputs, and the outputs kBatch records at a time.  One sequence of 200 tokens
+// (13 parts) takes 12 us per call, of 2,000 tokens 17 us and of 32,000 tokens
+// 36 us; with every record waited for in turn, every range between the parts
+// looked at with 64-bit divisions, and one merging wave per head for any number
+// of parts, they took 147, 615 and 1,274 us.
+template <typename T, int D, int S, int W, typename Rec>
+__device__ __forceinline__ void merge_records(const StreamArgs& a, int x0, int xs, int step, int n, bool final, int w,
+                                              int lane, T* out) {
+  constexpr int kChunks = S * D / 4;
+  constexpr int C = (kChunks + 63) / 64;  // chunks per lane
+  constexpr int kBatch = 8;
+  asm volatile("" ::: "memory");  // (the record loads stay below the arrival)
+  auto slot = [&](int i) {
+    const int x = xs + i * step;
+    return ((int64_t)x * 2 + (x == x0 ? 1 : 0)) * W + w;
+  };
+  f32x4_dev_t v[kBatch][C];
+  auto load = [&](int i0) {
 #pragma unroll
-  for (int j = 0; j < NH; ++j) { M[j] = kMInit; L[j] = 0.0f; }
+    for (int b = 0; b < kBatch; ++b) {  // (past the last record: that one again, unused)
+      const __amdgpu_buffer_rsrc_t r = record_rsrc(a.ws_o + slot(min(i0 + b, n - 1)) * S * D, S * D);
 #pragma unroll
-  for (int e = 0; e < E; ++e) acc[e] = 0.0f;
-  // pass 1: maxima
-  for (int64_t x = wg_first; x <= wg_last; ++x) {
-    if (U * x / G == U * (x + 1) / G) continue;  // empty range wrote nothing
-    const int64_t slot = (x * 2 + (x == wg_first ? 1 : 0)) * W + w;
-#pragma unroll
-    for (int j = 0; j < NH; ++j) M[j] = fmaxf(M[j], load_dev(a.ws_ml + slot * S * 2 + (h0 + j) * 2));
-  }
-  // pass 2: weighted sums
-  for (int64_t x = wg_first; x <= wg_last; ++x) {
-    if (U * x / G == U * (x + 1) / G) continue;
-    const int64_t slot = (x * 2 + (x == wg_first ? 1 : 0)) * W + w;
-    float c[NH];
-#pragma unroll
-    for (int j = 0; j < NH; ++j) {
-      float m, l;
-      load_dev2(a.ws_ml + slot * S * 2 + (h0 + j) * 2, m, l);
-      c[j] = fast_exp2(m - M[j]);
-      L[j] = fmaf(l, c[j], L[j]);
+      for (int u = 0; u < C; ++u) v[b][u] = load_dev4(r, (u * 64 + lane) * 4);
     }
-    const float* o = a.ws_o + slot * S * D;
-    float v[E];
-    if constexpr (E % 2 == 0) {
+  };
+  // lane i: record i's maxima and sums, then its weight for each head
+  float c[S], l[S], M[S];
+  {
+    const float* ml = a.ws_ml + slot(min(lane, n - 1)) * S * 2;
 #pragma unroll
-      for (int e = 0; e < E; e += 2) load_dev2(o + lane * E + e, v[e], v[e + 1]);
+    for (int j = 0; j < S; ++j) load_dev2(ml + j * 2, c[j], l[j]);
+  }
+  load(0);
+#pragma unroll
+  for (int j = 0; j < S; ++j) {
+    M[j] = across_groups_max<1>(fmaxf(kMInit, c[j]));
+    c[j] = fast_exp2(c[j] - M[j]);
+  }
+  auto bcast = [](float v, int i) {
+    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), i));
+  };
+  // Value of head h among the S wave-uniform ones.  (Chosen between as values:
+  // an array indexed at run time moves to LDS, and addressing it there reads
+  // the dispatch packet from host memory, 10 us for the grid's workgroups.)
+  auto pick = [&](const float (&v)[S], int h) {
+    float x = v[0];
+#pragma unroll
+    for (int j = 1; j < S; ++j) {
+      const float vj = v[j];
+      x = h == j ? vj : x;
+    }
+    return x;
+  };
+  float L[S];
+  f32x4_dev_t acc[C];
+#pragma unroll
+  for (int j = 0; j < S; ++j) L[j] = 0.0f;
+#pragma unroll
+  for (int u = 0; u < C; ++u) acc[u] = f32x4_dev_t{0.f, 0.f, 0.f, 0.f};
+  for (int i0 = 0; i0 < n; i0 += kBatch) {
+    if (i0 > 0) load(i0);
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b) {
+      if (i0 + b < n) {  // wave-uniform
+        float ci[S];
+#pragma unroll
+        for (int j = 0; j < S; ++j) {
+          ci[j] = bcast(c[j], i0 + b);
+          L[j] = fmaf(bcast(l[j], i0 + b), ci[j], L[j]);
+        }
+#pragma unroll
+        for (int u = 0; u < C; ++u) {
+          const float ch = pick(ci, Rec::head(u * 64 + lane));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[u][e] = fmaf(v[b][u][e], ch, acc[u][e]);
+        }
+      }
+    }
+  }
+  const __amdgpu_buffer_rsrc_t r = record_rsrc(a.ws_o + slot(0) * S * D, S * D);
+#pragma unroll
+  for (int u = 0; u < C; ++u) {
+    const int ch = u * 64 + lane;
+    if (final) {
+      const float Lh = pick(L, Rec::head(ch));
+      if (kChunks % 64 == 0 || ch < kChunks) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) store_out<T>(out + Rec::head(ch) * D + Rec::dim(ch) + e, acc[u][e] / Lh);
+      }
     } else {
-#pragma unroll
-      for (int e = 0; e < E; ++e) v[e] = load_dev(o + lane * E + e);
-    }
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int idx = lane * E + e;
-      acc[e] = fmaf(v[e], c[idx / D - h0], acc[e]);
+      store_dev4(r, ch * 4, acc[u]);  // (a chunk past the record is out of the descriptor's range)
     }
   }
+  if (!final && lane == 0) {
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int idx = lane * E + e;
-    store_out<T>(out + idx, acc[e] / L[idx / D - h0]);
+    for (int j = 0; j < S; ++j) store_dev(a.ws_ml + slot(0) * S * 2 + j * 2, M[j], L[j]);
   }
 }
 
@@ -87,24 +135,23 @@ __device__ __forceinline__ void merge_item(const StreamArgs& a, int64_t U, int64
 template <int S>
 struct HeldRecord {
   float m = 0.0f, l = 0.0f;
-  float o[mfma::kD / 16][4] = {};
+  f32x4_dev_t o[mfma::kD / 16] = {};
 };
 template <int S>
 __device__ __forceinline__ void load_held(HeldRecord<S>& r, const float* o, const float* ml, int lane) {
+  asm volatile("" ::: "memory");  // (the loads stay below the look at the counter)
+  const __amdgpu_buffer_rsrc_t rec = record_rsrc(o, S * mfma::kD);
   const int n = lane & 15, G = lane >> 4;
   if (n < S) {
     load_dev2(ml + n * 2, r.m, r.l);
 #pragma unroll
-    for (int mb = 0; mb < mfma::kD / 16; ++mb) {
-      load_dev2(o + n * mfma::kD + mb * 16 + 4 * G, r.o[mb][0], r.o[mb][1]);
-      load_dev2(o + n * mfma::kD + mb * 16 + 4 * G + 2, r.o[mb][2], r.o[mb][3]);
-    }
+    for (int mb = 0; mb < mfma::kD / 16; ++mb) r.o[mb] = load_dev4(rec, mfma::Record<S>::chunk(n, mb, G) * 4);
   }
 }
 
-// merge_item for an item of two parts whose first part is this wave's
+// merge_records for an item of two parts whose first part is this wave's
 // matrix-core state (its record never stored) and whose second part is the
-// record r: the same operations in the same order as merge_item over the two
+// record r: the same operations in the same order as merge_records over the two
 // records, so the output bits do not depend on which of the two parts merged.
 template <typename T, int S>
 __device__ __forceinline__ void merge_held(const mfma::State<S>& st, const HeldRecord<S>& r, int lane, T* out) {
@@ -124,37 +171,84 @@ __device__ __forceinline__ void merge_held(const mfma::State<S>& st, const HeldR
   }
 }
 
-// Count one part's arrival at an item's counter and return the parts counted
-// so far, this one included.  The counter's upper 48 bits carry the call's
-// token and its lower 16 bits the count: a counter left by an earlier call
-// (or found in a fresh workspace) holds another token and starts over at 1.
-// The first compare-and-swap guesses that the other parts (parts - 1) have
-// all arrived, so the last part, which goes on to merge, usually needs one
-// round trip; a wrong guess returns the counter's value and the loop goes on
-// from it.  It only repeats when another part of the same item changed the
-// counter in between, so it ends after at most as many rounds as the item
-// has parts, plus the guess; nothing here waits for another workgroup.
-__device__ __forceinline__ int arrive_count(unsigned long long* ctr, unsigned long long token, int parts) {
-  const unsigned long long tag = (token & 0xffffffffffffull) << 16;
-  unsigned long long old = tag | (unsigned long long)(parts - 1);
-  for (;;) {
-    const unsigned long long base = (old & ~0xffffull) == tag ? old : tag;
-    if (__hip_atomic_compare_exchange_strong(ctr, &old, base + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT))
-      return (int)((base + 1) & 0xffffull);
+// Arrival counters of cut items, one per range, counted once per workgroup.  A
+// counter's upper 48 bits carry the process's tag, its lower 16 bits the parts
+// counted; between calls it holds the tag and 0, left so by the part that
+// completed it, and a part counts with one fetch-and-add.  Anything else is
+// found only the first time a workspace (or that place of it) is used: the
+// parts that meet it put the tag in its place and count again, so nothing
+// needs clearing beforehand.  Device-scope atomics on one line complete about
+// 30 ns apart, so they are kept few: with every wave counting by itself, in a
+// compare-and-swap loop that retries once per other part, 8 sequences cut into
+// 26 parts each took 60 us.
+__device__ __forceinline__ bool counter_tagged(unsigned long long v, unsigned long long tag) {
+  return (v & ~0xffffull) == tag;
+}
+__device__ __forceinline__ void counter_reset(unsigned long long* ctr, unsigned long long tag) {
+  __hip_atomic_store(ctr, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Count one part and tell whether it completes the counter's n.
+__device__ __forceinline__ bool counter_arrive(unsigned long long* ctr, unsigned long long tag, int n) {
+  unsigned long long old = __hip_atomic_fetch_add(ctr, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  while (!counter_tagged(old, tag)) {
+    // (a failed swap met another part's; each changes the counter a bounded
+    // number of times, and once tagged it stays so)
+    unsigned long long now = old + 1;
+    while (!counter_tagged(now, tag) &&
+           !__hip_atomic_compare_exchange_strong(ctr, &now, tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT)) {
+    }
+    old = __hip_atomic_fetch_add(ctr, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  const bool last = (int)(old & 0xffffull) == n - 1;
+  if (last) counter_reset(ctr, tag);
+  return last;
 }
 
-// Range (of G equal ranges over U units) that holds unit e: the largest x
-// with floor(U x / G) <= e.
-__device__ __forceinline__ int64_t range_of(int64_t e, int64_t U, int64_t G) { return ((e + 1) * G - 1) / U; }
+// An item cut over ranges x0 .. x1 merges its n = x1 - x0 + 1 records at once
+// when n <= 16, and otherwise in two levels: the last part of each group of
+// ranges leaves the group's record in the place of its first, then counts the
+// group, so that no workgroup reads more than a group of records, or one per
+// group, alone.  Groups of 8 up to 64 parts, 16 up to 256, then 32: the two
+// levels then take about as many batches of records, and a level has at most
+// 64 records, one per lane.  The counters: x0's for the item; for a group, that
+// of its first range, or x0 + 1 for the first group.  Those ranges lie wholly
+// inside the item, so no other item uses their counters (a group of one range
+// needs none).
+struct CutItem {
+  int x0, x1;
+  __device__ bool grouped() const { return x1 - x0 >= 16; }
+  __device__ int shift() const { return x1 - x0 < 64 ? 3 : x1 - x0 < 256 ? 4 : 5; }
+  __device__ int group_first(int x) const { return x0 + ((x - x0) >> shift() << shift()); }
+  __device__ bool group_of_one(int x) const { return group_first(x) == x1; }
+  // level 0: range x's group; level 1: the item.  Its first record's range,
+  // the distance between records, their number, and the counter's range.
+  __device__ int first(int level, int x) const { return level == 0 ? group_first(x) : x0; }
+  __device__ int step(int level) const { return level == 1 && grouped() ? 1 << shift() : 1; }
+  __device__ int parts(int level, int x) const {
+    return level == 0 ? min(1 << shift(), x1 - group_first(x) + 1)
+                      : grouped() ? ((x1 - x0) >> shift()) + 1 : x1 - x0 + 1;
+  }
+  __device__ int counter(int level, int x) const { return first(level, x) + (level == 0 && group_first(x) == x0 ? 1 : 0); }
+};
+static_assert(kStreamMaxGrid <= 32 * 64, "one record per lane at either level");
+
+// First unit of range x, and the range that holds unit e (the largest x with
+// U x / G <= e), of G equal ranges over U units.  U <= kStreamMaxUnits *
+// kStreamMaxGrid = 2^21 (the host plans the grid for that) and x <= G <= 2^10,
+// so the products fit 32 bits.
+__device__ __forceinline__ int range_begin(int x, int U, int G) { return (int)((uint32_t)U * (uint32_t)x / (uint32_t)G); }
+__device__ __forceinline__ int range_of(int e, int U, int G) {
+  return (int)(((uint32_t)(e + 1) * (uint32_t)G - 1u) / (uint32_t)U);
+}
+static_assert((int64_t)kStreamMaxUnits * kStreamMaxGrid * kStreamMaxGrid <= 0xffffffffll, "32-bit range products");
 
 // Sequence of unit u: the largest r with nb * cum[r] <= u (a non-empty one).
-__device__ __forceinline__ int info_row_seq(const int32_t* cum, int R, int nb, int64_t u) {
+__device__ __forceinline__ int info_row_seq(const int32_t* cum, int R, int nb, int u) {
   int lo = 0, hi = R - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if ((int64_t)nb * cum[mid] <= u) lo = mid; else hi = mid - 1;
+    if (nb * cum[mid] <= u) lo = mid; else hi = mid - 1;
   }
   return lo;
 }
@@ -167,6 +261,9 @@ struct StreamSmem {
   int32_t page[kStreamMaxUnits];    // unit table of the range: page id
   int32_t info[kStreamMaxUnits];    //   and info word
   int32_t scan[64 * W];
+  CutItem cut[2];                   // the items cut by the range's start and by its end (x0 = -1: none)
+  int32_t last[2];                  // whether this workgroup's part of each completed its counter
+  int32_t held;                     // whether the last item's other part has counted
   __attribute__((aligned(16))) uint8_t kv[MF ? W : 1][MF ? 2 * mfma::kTile : 16];  // per-wave tile staging
 };
 
@@ -215,8 +312,12 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
     if (tid == NT - 1) s_cum[R] = off + local;
     __syncthreads();
   }
-  const int64_t U = (int64_t)a.nb * s_cum[R];
-  const int64_t G = G_;
+  const int U = a.nb * s_cum[R];
+  // A batch of fewer units than workgroups runs on the first U of them, one
+  // unit each (no range is ever empty).  Ranges of at least two or three units
+  // save parts to merge but stream alone for longer: within 3 % on most small
+  // batches, 35 % slower on 8 sequences of 20 to 60 tokens.
+  const int G = max(1, min(G_, U));
   // Rows without units: zeros for an empty decode context, NaN for a contract
   // violation (flagged in s_tail above); rows r = bid (mod G) are this
   // workgroup's to write.
@@ -229,22 +330,27 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
     T* o = reinterpret_cast<T*>(a.out) + (int64_t)qrow * a.H_q * D;
     for (int i = tid; i < a.H_q * D; i += NT) store_out<T>(o + i, fill);
   }
-  const int64_t u0 = U * bid / G, u1 = U * (bid + 1) / G;
-  const int n_units = (int)(u1 - u0);
-  if (n_units <= 0) return;
+  if (bid >= G || U == 0) return;
+  const int u0 = range_begin(bid, U, G), u1 = range_begin(bid + 1, U, G);
+  const int n_units = u1 - u0;
 
-  // 2. unit table of this range
+  // 2. unit table of this range, and the items cut by its start and its end
   const BlockTable bt{a.block_table, a.bt_stride};
   for (int i = tid; i < n_units; i += NT) {
-    const int64_t u = u0 + i;
+    const int u = u0 + i;
     const int r = info_row_seq(s_cum, R, a.nb, u);
     const int np = s_cum[r + 1] - s_cum[r];
-    const int rem = (int)(u - (int64_t)a.nb * s_cum[r]);
+    const int rem = u - a.nb * s_cum[r];
     const int hb = rem / np, p = rem - hb * np;
     const int qrow = a.query_start_loc != nullptr ? a.query_start_loc[r] : r;
     s_page[i] = bt.page(r, p);
     const int valid = p == np - 1 ? (int)s_tail[r] : kPage;
     s_info[i] = valid | (p == 0) << 5 | (p == np - 1) << 6 | hb << 7 | qrow << 13;
+    if (i == 0 || i == n_units - 1) {
+      const CutItem cut{range_of(u - p, U, G), range_of(u - p + np - 1, U, G)};
+      if (i == 0) sm.cut[0] = p == 0 ? CutItem{-1, -1} : cut;
+      if (i == n_units - 1) sm.cut[1] = p == np - 1 ? CutItem{-1, -1} : cut;
+    }
   }
   __syncthreads();
 
@@ -277,7 +383,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
           // (sequence, head block, page) of the unit, from the unit's index
           const int r = info_row_seq(s_cum, R, a.nb, u0 + k);
           const int np = s_cum[r + 1] - s_cum[r];
-          const int rem = (int)(u0 + k - (int64_t)a.nb * s_cum[r]);
+          const int rem = u0 + k - a.nb * s_cum[r];
           const int hb = rem / np, p = rem - hb * np;
           if (lane < valid)
             trace_put(a.trace, ((int64_t)(hb * W + w) * R + r) * (a.bt_stride * kPage) + p * kPage + lane,
@@ -294,34 +400,56 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
   };
 
   // Items cut by range boundaries.  Every part (the item's first part ends
-  // its range; a later part starts one) stores its partial record, then
-  // counts its arrival at the item's counter; the part that arrives last
-  // merges all the records in range order and writes the output.  Nothing
-  // waits on another workgroup, so the result and the kernel's completion do
-  // not depend on how many workgroups are resident or in which order they
-  // run.  Records travel through device-coherent stores and loads; a part
-  // counts itself only once its record stores have completed.
-  auto arrive = [&](int64_t x0, int64_t x1, int qrow, int g) {
-    int parts = 0;
-    for (int64_t x = x0; x <= x1; ++x) parts += U * x / G != U * (x + 1) / G ? 1 : 0;
-    int got = 0;
-    if (lane == 0) got = arrive_count(a.ws_flag + x0 * W + w, a.token, parts);
-    got = __builtin_amdgcn_readfirstlane(got);
-    if (got == parts) {
-      T* outp = reinterpret_cast<T*>(a.out) + ((int64_t)qrow * a.H_q + (int64_t)g * S) * D;
-      merge_item<T, D, S, W>(a, U, G, x0, x1, w, lane, outp);
+  // its range; a later part starts one) stores its partial records, one per
+  // wave, and then counts its arrival; the workgroup whose part arrives last
+  // merges the records in range order and writes the output.  Nothing waits on
+  // another workgroup, so the result and the kernel's completion do not depend
+  // on how many workgroups are resident or in which order they run.  Records
+  // travel through device-coherent stores and loads.
+  //
+  // A range leaves at most two records per wave: job 0, the item cut by its
+  // start, and job 1, that cut by its end (a range inside one item has only
+  // job 0).  A job moves one phase at a time, at the barriers that the units
+  // have anyway: record stores issued (1), completed in every wave (2), counted
+  // by wave 0 (3).  A part that was the last merges when the range has
+  // streamed, where no tile is held in registers and a merge can keep many
+  // records in flight (4).
+  int phase[2] = {0, 0}, level[2] = {1, 1}, job_row[2] = {0, 0}, job_g[2] = {0, 0};
+  auto of_job = [](int j, int v0, int v1) { return j == 0 ? v0 : v1; };
+  auto job_begin = [&](auto j_, int qrow, int g) {
+    constexpr int j = decltype(j_)::value;
+    const CutItem cut = sm.cut[j];
+    phase[j] = 1;
+    level[j] = cut.grouped() && !cut.group_of_one(bid) ? 0 : 1;
+    job_row[j] = qrow;
+    job_g[j] = g;
+  };
+  // (wait: the s_waitcnt encoding that leaves only the loads just issued
+  // outstanding, as a std::integral_constant: waiting for the record stores
+  // then does not drain them, since the vector-memory counter retires in
+  // issue order)
+  auto jobs_stored = [&](auto wait) {
+    if (phase[0] == 1 || phase[1] == 1) {  // wave-uniform
+      asm volatile("" ::: "memory");  // (the record stores stay above)
+      __builtin_amdgcn_s_waitcnt(decltype(wait)::value);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) phase[j] = phase[j] == 1 ? 2 : phase[j];
     }
   };
-
-  // A part whose record is stored at unit k < n_units - 1 counts its arrival
-  // one unit later, once the loads issued after the record are the only ones
-  // outstanding: waiting for the record stores then does not drain the tile
-  // loads in flight (the vector-memory counter retires loads and stores in
-  // issue order).
-  bool pending = false;  // (wave-uniform) an arrival to count at the next unit
-  int64_t pend_x0 = 0, pend_x1 = 0;
-  int pend_row = 0, pend_g = 0;
-
+  auto jobs_step = [&]() {  // after a barrier
+    if ((phase[0] | phase[1]) < 2) return;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) phase[j] = phase[j] == 3 ? sm.last[j] ? 4 : 0 : phase[j];
+    if (w == 0 && lane < 2) {
+      const int ph = of_job(lane, phase[0], phase[1]), lv = of_job(lane, level[0], level[1]);
+      if (ph == 2) {
+        const CutItem cut = sm.cut[lane];
+        sm.last[lane] = counter_arrive(a.ws_flag + (int64_t)cut.counter(lv, bid) * W, a.tag, cut.parts(lv, bid));
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) phase[j] = phase[j] == 2 ? 3 : phase[j];
+  };
   // Range-end merge from registers (the matrix-core split loop sets these):
   // the item ending the range has one other part, which has counted, and
   // its record is in held_rec.
@@ -335,6 +463,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
   // A new (row, head) item loads its queries.  Returns the unit's info word.
   auto begin_unit = [&](int k) {
     __syncthreads();
+    jobs_step();
     int info = 0;
     if (k < n_units) {
       info = __builtin_amdgcn_readfirstlane(s_info[k]);
@@ -361,8 +490,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
   };
   // End of unit k (k < n_units): an item that ends here is finished in place
   // when it lies wholly in the range; a part cut by the range stores its
-  // record and counts its arrival (at the next unit, or now at the range's
-  // last unit).
+  // record and begins its job.
   auto end_unit = [&](int k, int info) {
     const bool tail_partial = k == n_units - 1 && !info_end(info);
     if (info_end(info) || k == n_units - 1) {
@@ -374,10 +502,11 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
           mfma::finish<S, T>(ms, lane, outp);
         else
           finish_rows<T, D, S>(st, row, dl, outp);
-      } else {  // (workgroup-uniform, but for merge_held)
+      } else {  // (workgroup-uniform)
         if constexpr (MF) {
-          if (held_now && k == n_units - 1) {  // (wave-uniform)
+          if (held_now && k == n_units - 1) {
             merge_held<T, S>(ms, held_rec, lane, outp);
+            if (tid == 0) counter_reset(a.ws_flag + (int64_t)bid * W, a.tag);
             return;
           }
         }
@@ -386,30 +515,33 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
           mfma::partial<S>(ms, lane, a.ws_o + slot * S * D, a.ws_ml + slot * S * 2);
         else
           partial_rows<T, D, S>(st, row, dl, lane, a.ws_o + slot * S * D, a.ws_ml + slot * S * 2);
-        // the item's first and last units, and the ranges holding them
-        const int rr = info_row_seq(s_cum, R, a.nb, u0 + k);
-        const int np = s_cum[rr + 1] - s_cum[rr];
-        const int64_t e_first = (int64_t)a.nb * s_cum[rr] + (int64_t)info_hb(info) * np;
-        pend_x0 = range_of(e_first, U, G);
-        pend_x1 = range_of(e_first + np - 1, U, G);
-        pend_row = r;
-        pend_g = g;
-        if (k + 1 < n_units) {
-          pending = true;  // counted at the next unit
-        } else {
-          __builtin_amdgcn_s_waitcnt(0);  // the record stores have completed
-          arrive(pend_x0, pend_x1, pend_row, pend_g);
-        }
+        if (head_partial) job_begin(std::integral_constant<int, 0>{}, r, g);
+        else job_begin(std::integral_constant<int, 1>{}, r, g);
       }
     }
   };
-  // (wait: the s_waitcnt encoding that leaves only the loads just issued
-  // outstanding, as a std::integral_constant)
-  auto arrive_pending = [&](auto wait) {
-    if (pending) {  // wave-uniform
-      pending = false;
-      __builtin_amdgcn_s_waitcnt(decltype(wait)::value);
-      arrive(pend_x0, pend_x1, pend_row, pend_g);
+  // The jobs left when the range has streamed.
+  auto jobs_finish = [&]() {
+    while (phase[0] | phase[1]) {  // workgroup-uniform
+      jobs_stored(std::integral_constant<int, 0>{});
+      __syncthreads();
+      jobs_step();
+#pragma unroll 1
+      for (int j = 0; j < 2; ++j) {
+        if (of_job(j, phase[0], phase[1]) != 4) continue;
+        const int lv = of_job(j, level[0], level[1]);
+        const CutItem cut = sm.cut[j];
+        T* outp = reinterpret_cast<T*>(a.out) + ((int64_t)of_job(j, job_row[0], job_row[1]) * a.H_q +
+                                                 (int64_t)of_job(j, job_g[0], job_g[1]) * S) * D;
+        using Rec = std::conditional_t<MF, mfma::Record<S>, RowsRecord<D, S>>;
+        merge_records<T, D, S, W, Rec>(a, cut.x0, cut.first(lv, bid), cut.step(lv), cut.parts(lv, bid), lv == 1, w,
+                                       lane, outp);
+        // (a group's record counts in the item next)
+        phase[0] = j == 0 ? 1 - lv : phase[0];
+        phase[1] = j == 1 ? 1 - lv : phase[1];
+        level[0] = j == 0 ? 1 : level[0];
+        level[1] = j == 1 ? 1 : level[1];
+      }
     }
   };
 
@@ -452,37 +584,33 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
     //
     // The range's last item, when cut by the range's end, usually finishes
     // last: its other part started the next range and counted long before.
-    // If that item has two parts (it ends in the next range), its counter is
-    // loaded (inline assembly too) when the next-to-last unit's QK half
-    // starts, older than the K loads of the last unit, so the waits above
-    // cover it unchanged; it is looked at when the last unit starts; if the
-    // other part has counted, its record is loaded then, and the last unit
-    // ends by merging from registers (merge_held): no record stored, no
-    // arrival counted (every other part has counted, so no part reads the
+    // If that item has two parts (it ends in the next range), wave 0 loads its
+    // counter (inline assembly too) in the next-to-last unit's QK half, older
+    // than the K loads of the last unit, so the waits above cover it
+    // unchanged, and looks at it at that unit's end; if the other part has
+    // counted, every wave loads its record when the last unit starts, and the
+    // last unit ends by merging from registers (merge_held): no record stored,
+    // no arrival counted (every other part has counted, so no part reads the
     // counter again in this call), the record's latency hidden behind the
-    // unit's fold.  With a single unit the counter load goes out between
-    // its K and V loads.
-    bool held = false;  // (wave-uniform) the range's last item qualifies
-    {
-      const int info_l = __builtin_amdgcn_readfirstlane(s_info[n_units - 1]);
-      if (!info_end(info_l)) {
-        const int rr = info_row_seq(s_cum, R, a.nb, u1 - 1);
-        const int np = s_cum[rr + 1] - s_cum[rr];
-        const int64_t e_first = (int64_t)a.nb * s_cum[rr] + (int64_t)info_hb(info_l) * np;
-        held = e_first >= u0 && range_of(e_first + np - 1, U, G) == bid + 1;
-      }
-    }
-    const unsigned long long* ctr_p = a.ws_flag + (int64_t)bid * W + w;
-    const unsigned long long counted = ((a.token & 0xffffffffffffull) << 16) | 1ull;  // one part counted
+    // unit's fold.  With a single unit the counter is loaded between its K and
+    // V loads and looked at before it starts.
+    const bool held = sm.cut[1].x0 == bid && sm.cut[1].x1 == bid + 1;
+    const unsigned long long counted = a.tag | 1ull;  // one part counted
     u32x2_t ctr = u32x2_t{0u, 0u};
 
     u32x4 kc[Sh::NI], vc[Sh::NI];
     load_queries(__builtin_amdgcn_readfirstlane(s_info[0]));
     tile_k(0, kc);
-    if (held && n_units == 1) asm_load_dev(ctr_p, ctr);
+    if (held && w == 0 && n_units == 1) asm_load_dev(a.ws_flag + (int64_t)bid * W, ctr);
     tile_v(0, vc);
+    auto look = [&](auto newer) {  // newer: the tile loads issued after the counter's
+      vm_wait<decltype(newer)::value>(ctr);
+      if (lane == 0) sm.held = ((unsigned long long)ctr.y << 32 | ctr.x) == counted;
+    };
+    if (held && w == 0 && n_units == 1) look(std::integral_constant<int, Sh::NI>{});
     for (int k = 0; k < n_units; ++k) {
       __syncthreads();  // lockstep, as in begin_unit
+      jobs_step();
       const int info = __builtin_amdgcn_readfirstlane(s_info[k]);
       if (info_start(info) || k == 0) {
         head_partial = !info_start(info);
@@ -490,11 +618,9 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
       }
       vm_wait<Sh::NI>(kc);  // K of unit k and the queries (issued before it)
       vm_wait<Sh::NI>(ms.qt);
-      if (held && k + 2 == n_units) asm_load_dev(ctr_p, ctr);
+      if (held && w == 0 && k + 2 == n_units) asm_load_dev(a.ws_flag + (int64_t)bid * W, ctr);
       if (held && k == n_units - 1) {
-        vm_wait<Sh::NI>(ctr);  // (issued before unit k's V loads)
-        held_now = __builtin_amdgcn_readfirstlane(ctr.x) == (uint32_t)counted &&
-                   __builtin_amdgcn_readfirstlane(ctr.y) == (uint32_t)(counted >> 32);
+        held_now = sm.held;
         if (held_now) {
           const int64_t slot = ((int64_t)(bid + 1) * 2 + 0) * W + w;
           load_held<S>(held_rec, a.ws_o + slot * S * D, a.ws_ml + slot * S * 2, lane);
@@ -507,13 +633,15 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
         if (info_start(next)) load_queries(next);
       }
       tile_k(k + 1, kc);
-      arrive_pending(std::integral_constant<int, (Sh::NI & 15) | (7 << 4) | (15 << 8)>{});
+      jobs_stored(std::integral_constant<int, (Sh::NI & 15) | (7 << 4) | (15 << 8)>{});
       vm_wait<Sh::NI>(vc);  // V of unit k
       mfma::fold_pv<S>(ms, vc, s_kv[w], lane, phi, plo);
       tile_v(k + 1, vc);
       end_unit(k, info);
+      if (held && w == 0 && k + 2 == n_units) look(std::integral_constant<int, 2 * Sh::NI>{});
     }
     __builtin_amdgcn_s_waitcnt(0);  // the last (null) tiles' loads
+    jobs_finish();
   } else {
     // A ring of NBUF register tiles: the tile of unit k + NBUF - 1 is issued
     // at the start of unit k.
@@ -529,7 +657,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
         const int k = base + u;
         const int info = begin_unit(k);
         issue(kr[(u + NBUF - 1) % NBUF], vr[(u + NBUF - 1) % NBUF], k + NBUF - 1);
-        arrive_pending(std::integral_constant<int, kWaitRing>{});
+        jobs_stored(std::integral_constant<int, kWaitRing>{});
         if (k < n_units) {
           if constexpr (MF)
             mfma::fold<S>(ms, kr[u], vr[u], s_kv[w], lane, info_valid(info), a.scale_log2);
@@ -539,6 +667,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
         }
       }
     }
+    jobs_finish();
   }
 }
 

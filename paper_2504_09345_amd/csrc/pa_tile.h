@@ -273,7 +273,13 @@ __device__ __forceinline__ void finish_rows(const DecodeState<T, D, S>& st, int 
   }
 }
 
-// Partial record of one item: unnormalised O [S][D], then (M, L) per head.
+// Partial record of one item: unnormalised O in 16-byte chunks (head c / (D /
+// 4), dims 4 (c mod D / 4) .. +3 of chunk c: [S][D]), then (M, L) per head.
+template <int D, int S>
+struct RowsRecord {
+  static __device__ __forceinline__ int head(int c) { return c / (D / 4); }
+  static __device__ __forceinline__ int dim(int c) { return c % (D / 4) * 4; }
+};
 template <typename T, int D, int S>
 __device__ __forceinline__ void partial_rows(const DecodeState<T, D, S>& st, int row, int dl, int lane, float* o,
                                              float* ml) {
@@ -281,10 +287,12 @@ __device__ __forceinline__ void partial_rows(const DecodeState<T, D, S>& st, int
   float M[S], L[S], O[S][Sh::VEC];
   merge_rows<T, D, S>(st, M, L, O);
   if (row == 0) {
+    const __amdgpu_buffer_rsrc_t r = record_rsrc(o, S * D);
 #pragma unroll
     for (int j = 0; j < S; ++j) {
 #pragma unroll
-      for (int e = 0; e < Sh::VEC; e += 2) store_dev(o + j * D + dl * Sh::VEC + e, O[j][e], O[j][e + 1]);
+      for (int e = 0; e < Sh::VEC; e += 4)
+        store_dev4(r, j * D + dl * Sh::VEC + e, f32x4_dev_t{O[j][e], O[j][e + 1], O[j][e + 2], O[j][e + 3]});
     }
   }
   if (lane == 0) {
@@ -480,19 +488,24 @@ __device__ __forceinline__ void finish(const State<S>& st, int lane, T* out) {
   }
 }
 
-// Partial record: unnormalised O [s][D] and (M, L) per head (device-coherent
-// stores: the record is read by another workgroup of the same launch).
+// Partial record: unnormalised O in 16-byte chunks in the accumulators' order
+// (chunk c: head c / 4 mod s, dims 16 (c / 4 s) + 4 (c mod 4) .. +3, so the
+// lanes of one store write adjacent chunks) and (M, L) per head.
+template <int S>
+struct Record {
+  static __device__ __forceinline__ int head(int c) { return c / 4 % S; }
+  static __device__ __forceinline__ int dim(int c) { return c / (4 * S) * 16 + c % 4 * 4; }
+  // chunk of head n, accumulator mb, lane group G
+  static __device__ __forceinline__ int chunk(int n, int mb, int G) { return (mb * S + n) * 4 + G; }
+};
 template <int S>
 __device__ __forceinline__ void partial(const State<S>& st, int lane, float* o, float* ml) {
   const float L = total_l(st);
   const int n = lane & 15, G = lane >> 4;
+  const __amdgpu_buffer_rsrc_t r = record_rsrc(o, S * kD);
   if (n < S) {
 #pragma unroll
-    for (int mb = 0; mb < kD / 16; ++mb) {
-      const int d = mb * 16 + 4 * G;
-      store_dev(o + n * kD + d, st.acc[mb][0], st.acc[mb][1]);
-      store_dev(o + n * kD + d + 2, st.acc[mb][2], st.acc[mb][3]);
-    }
+    for (int mb = 0; mb < kD / 16; ++mb) store_dev4(r, Record<S>::chunk(n, mb, G) * 4, st.acc[mb]);
     if (G == 0) store_dev(ml + n * 2, st.m, L);
   }
 }

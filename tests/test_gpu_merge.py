@@ -1,0 +1,96 @@
+"""Items cut over several stream-K ranges and merged in the launch: the numbers
+of parts at which the merge changes form (one batch of records, two, groups of
+8, 16 and 32), whatever the workspace holds beforehand, and a recorded launch
+replayed."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2504_09345_amd import binding as pb
+from paper_2504_09345_amd import workloads as W
+
+from parity_util import announce, assert_parity, run_oracle, upload
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(b, dev, ws):
+    out = torch.full_like(dev["q"], float("nan"))
+    dims = pb.make_dims(dev["q"], dev["k"], dev["bt"], int(b.context_lens.max()))
+    pb.paged_attn(dev["q"], dev["k"], dev["v"], dev["bt"], dev["cl"], b.scale, out, dims, workspace=ws)
+    torch.cuda.synchronize()
+    return out.float().cpu().numpy()
+
+
+# one sequence of as many pages as its item has parts (one unit per range, up
+# to the grid: 208 workgroups with 8 KV heads, more ranges with fewer)
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("bf16", 64), ("fp32", 128)])
+@pytest.mark.parametrize("H_kv,s,pages", [
+    (8, 4, 2), (8, 6, 8), (8, 8, 9), (8, 4, 16), (8, 1, 17), (8, 4, 64), (8, 2, 65), (8, 4, 208), (8, 4, 500),
+    (1, 4, 256), (1, 8, 257), (2, 6, 500), (4, 1, 1000)])
+def test_parts(dtype, D, H_kv, s, pages):
+    announce(f"merge {dtype} D={D} H_kv={H_kv} s={s} pages={pages}")
+    b = W.generate("tiny", seed=pages, dtype=dtype, overrides=dict(
+        H_q=s * H_kv, H_kv=H_kv, D=D, ctx=("list", [16 * pages - 3]), pool=("factor", 1.2)))
+    dev = upload(b)
+    n = pb.pa_workspace_size(pb.make_dims(dev["q"], dev["k"], dev["bt"], 16 * pages))
+    ws = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    got = _run(b, dev, ws)
+    # (sums of up to 8,000 fp32 terms: the tolerance is that of the strict floor
+    # only for short contexts)
+    assert_parity(got, run_oracle(b), strict=False, what=f"{pages} parts")
+    again = _run(b, dev, ws)  # the counters as the first call left them
+    assert np.array_equal(got.view(np.uint32), again.view(np.uint32))
+    for fill in (0xFF, 0x01, None):  # NaN, small counts, random bytes
+        ws = (torch.randint(0, 256, (n,), dtype=torch.uint8, device="cuda") if fill is None
+              else torch.full((n,), fill, dtype=torch.uint8, device="cuda"))
+        again = _run(b, dev, ws)
+        assert np.array_equal(got.view(np.uint32), again.view(np.uint32)), fill
+
+
+def test_two_cut_items_per_range_and_head_blocks():
+    """Ranges of two or three units that end one item and start the next, with
+    two head blocks per page: both records of a range counted at its end."""
+    announce("two cut items per range")
+    b = W.generate("tiny", seed=3, overrides=dict(H_q=64, H_kv=16, D=128, ctx=("list", [83 + 5 * i for i in range(40)]),
+                                                  pool=("factor", 1.2)))
+    dev = upload(b)
+    ws = torch.randint(0, 256, (pb.pa_workspace_size(pb.make_dims(dev["q"], dev["k"], dev["bt"], 278)),),
+                       dtype=torch.uint8, device="cuda")
+    got = _run(b, dev, ws)
+    assert_parity(got, run_oracle(b), what="two cut items")
+    for _ in range(8):
+        assert np.array_equal(got.view(np.uint32), _run(b, dev, ws).view(np.uint32))
+
+
+def test_recorded_launch_replays():
+    """A captured call replayed several times, with and without other calls
+    between the replays, gives the eager result each time."""
+    announce("graph replay")
+    b = W.generate("tiny", seed=4, overrides=dict(H_q=32, H_kv=8, D=128, ctx=("list", [300, 2000, 45, 16]),
+                                                  pool=("factor", 1.2)))
+    dev = upload(b)
+    qsl = torch.arange(b.num_seqs + 1, dtype=torch.int32, device="cuda")
+    dims = pb.make_dims(dev["q"], dev["k"], dev["bt"], 2000, num_q_rows=b.num_seqs, max_q_len=1)
+    out = torch.zeros_like(dev["q"])
+
+    def call():
+        pb.paged_attn_varlen_noalloc(dev["q"], dev["k"], dev["v"], dev["bt"], dev["cl"], qsl, b.scale, out, dims)
+
+    call()
+    torch.cuda.synchronize()
+    ref = out.clone()
+    assert_parity(ref.float().cpu().numpy(), run_oracle(b), what="eager")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for i in range(6):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref), f"replay {i}"
+        if i % 2:
+            out.zero_()
+            call()
+            torch.cuda.synchronize()
+            assert torch.equal(out, ref), f"eager after replay {i}"
