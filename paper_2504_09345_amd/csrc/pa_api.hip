@@ -242,21 +242,31 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
     // batch 256 213-214 us per launch at 208 workgroups, 214-217 at 192, 218
     // at 256, 231 at 160; DBRX and 32k contexts within 0.5 % from 192 to 208,
     // 1-2 % slower at 256.
+    // That is with 64 KiB of tiles in flight per CU (bf16, head_dim 128, 8
+    // waves).  Kernels with half of that or less in flight, or whose fold is
+    // on the VALU, stream faster from every CU: bf16 head_dim 64 at batch 128
+    // 73 us at 13/16 and 68.6 at 16/16 (batch 64, 4k-20k tokens: 260 and 233),
+    // fp32 batch 64 106 and 103 us.
     // A batch whose ranges would overflow the LDS unit table takes more
     // workgroups (up to kStreamMaxGrid), even beyond one wave of resident
     // workgroups: no workgroup waits for another, so any residency works.
-    int64_t g = (int64_t)per_cu * cus * kStreamCuNum / kStreamCuDen;
-    if (g < 1) g = 1;
-    if (g < p.g_min) g = p.g_min;
-    if (g > pa::kStreamMaxGrid) g = pa::kStreamMaxGrid;
-    G = (int)g;
-    // workspace layout of this call: records and counters of G ranges, then
+    // Workspace layout of this call: records and counters of G ranges, then
     // the split-K partials (a caller's workspace, sized for kStreamMaxGrid
-    // ranges, always holds it)
-    const size_t recs = (size_t)G * 2 * p.W * p.s;
-    p.st_o = align256(recs * (size_t)dims->head_dim * sizeof(float));
-    p.st_ml = align256(recs * 2 * sizeof(float));
-    p.st_cum = align256((size_t)G * p.W * sizeof(unsigned long long));
+    // ranges, always holds it; the fixed scratch may hold the smaller grid
+    // only).
+    const bool all_cus = dims->dtype != PA_BF16 || dims->head_dim != 128 || p.W < 8;
+    for (const bool all : {all_cus, false}) {
+      int64_t g = (int64_t)per_cu * cus * (all ? 1 : kStreamCuNum) / (all ? 1 : kStreamCuDen);
+      if (g < 1) g = 1;
+      if (g < p.g_min) g = p.g_min;
+      if (g > pa::kStreamMaxGrid) g = pa::kStreamMaxGrid;
+      G = (int)g;
+      const size_t recs = (size_t)G * 2 * p.W * p.s;
+      p.st_o = align256(recs * (size_t)dims->head_dim * sizeof(float));
+      p.st_ml = align256(recs * 2 * sizeof(float));
+      p.st_cum = align256((size_t)G * p.W * sizeof(unsigned long long));
+      if (p.st_o + p.st_ml + p.st_cum + p.sp_o + p.sp_ml <= workspace_bytes) break;
+    }
     sa.q = q;
     sa.k_pages = k_pages;
     sa.v_pages = v_pages;

@@ -94,7 +94,7 @@ constexpr int kStreamMaxWaves = PA_STREAM_MAX_WAVES;  // waves (KV heads) per st
 #ifndef PA_STREAM_MFMA
 #define PA_STREAM_MFMA 1
 #endif
-constexpr bool kStreamMfma = PA_STREAM_MFMA != 0;  // bf16 D = 128 tiles on the matrix cores
+constexpr bool kStreamMfma = PA_STREAM_MFMA != 0;  // bf16 tiles on the matrix cores
 
 // Optional events bracketing one kernel's execution (hipExtLaunchKernel's
 // start/stop events: taken when the kernel starts and ends, not when the

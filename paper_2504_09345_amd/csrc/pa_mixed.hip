@@ -19,11 +19,12 @@ namespace pa {
 
 namespace {
 
+constexpr int kMixedD = 128;
 constexpr int kMixedW = 8;  // decode waves per workgroup = prefill waves
 static_assert(64 * kMixedW == kPfThreads, "decode and prefill workgroups must match");
 
 union MixedSmem {
-  StreamSmem<kMixedW, true> dec;
+  StreamSmem<kMixedW, kMixedD, true> dec;
   struct {
     PrefillSmem smem;
     int32_t cum[kStreamMaxRows + 1];
@@ -34,9 +35,9 @@ template <int S, bool TR>
 __global__ __launch_bounds__(64 * kMixedW) void mixed_kernel(StreamArgs sa, PrefillArgs pa_, int G_dec) {
   __shared__ MixedSmem sm;
   if ((int)blockIdx.x < G_dec)
-    stream_body<uint16_t, mfma::kD, S, kMixedW, kStreamRing, true, TR, false>(sa, sm.dec, blockIdx.x, G_dec);
+    stream_body<uint16_t, kMixedD, S, kMixedW, kStreamRing, true, TR, false>(sa, sm.dec, blockIdx.x, G_dec);
   else
-    prefill_body<mfma::kD, S, TR>(pa_, sm.pf.smem, sm.pf.cum, blockIdx.x - G_dec, gridDim.x - G_dec);
+    prefill_body<kMixedD, S, TR>(pa_, sm.pf.smem, sm.pf.cum, blockIdx.x - G_dec, gridDim.x - G_dec);
 }
 
 template <bool TR>
@@ -57,7 +58,7 @@ const void* mixed_fn(int s, bool trace = false) { return trace ? mixed_pick<true
 }  // namespace
 
 bool mixed_supported(int dtype, int D, int s, int W) {
-  return kStreamMfma && dtype == 0 && D == mfma::kD && W == kMixedW && mixed_fn(s) != nullptr;
+  return kStreamMfma && dtype == 0 && D == kMixedD && W == kMixedW && mixed_fn(s) != nullptr;
 }
 
 hipError_t launch_mixed(int s, const StreamArgs& sa, const PrefillArgs& pa_, int G_dec, int G, hipStream_t st,

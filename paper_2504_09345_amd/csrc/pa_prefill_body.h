@@ -33,8 +33,8 @@ constexpr int kPfLoadPolicy = 0;
 
 // LDS of one prefill workgroup (besides the per-sequence item prefix sums).
 struct PrefillSmem {
-  __attribute__((aligned(16))) uint8_t k[kPfLdsSteps][kPfStep * kPage * mfma::kD * 2];
-  __attribute__((aligned(16))) uint8_t v[kPfLdsSteps][kPfStep * kPage * mfma::kD * 2];
+  __attribute__((aligned(16))) uint8_t k[kPfLdsSteps][kPfStep * kPage * 128 * 2];
+  __attribute__((aligned(16))) uint8_t v[kPfLdsSteps][kPfStep * kPage * 128 * 2];
   int32_t bt[kPfMaxPages];
   int32_t scan[kPfThreads];
   int32_t vwide;  // the item needs the bf16 pass (non-finite or tiny output rows after the fp16 pass)
@@ -46,7 +46,7 @@ struct PrefillSmem {
 template <int D, int S, bool TR = false>
 __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& sm, int32_t* s_cum, int bid,
                                              int G) {
-  static_assert(D == mfma::kD, "prefill MFMA path is built for head_dim 128");
+  static_assert(D == 128, "prefill MFMA path is built for head_dim 128");
   constexpr int PB = kPfRows / S;       // chunk positions per item
   constexpr int KSTEPS = D / 32;        // QK MFMA steps over dims
   constexpr int MB = D / 16;            // PV MFMA blocks over dims
@@ -91,8 +91,8 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
   // st_pg of a step (st_pg is wave-uniform)
   const int st_pg = w / (kPfWaves / kPfStep), st_j = tid % (kPage * C16);
   const int st_key = st_j / C16, st_c = st_j % C16;
-  const int st_off = st_pg * KT + mfma::swz(st_key, st_c);
-  const int st_off_v = st_pg * KT + mfma::swz_v(st_key, st_c);
+  const int st_off = st_pg * KT + mfma::swz<D>(st_key, st_c);
+  const int st_off_v = st_pg * KT + mfma::swz_v<D>(st_key, st_c);
   const int st_ld = st_j * 16;  // byte offset in the global tile
   const int n = lane & 15, Gq = lane >> 4;  // MFMA column (query row of a block) and lane group
 
@@ -205,7 +205,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
       for (int pp = 0; pp < kPfStep; ++pp)
 #pragma unroll
         for (int st = 0; st < KSTEPS; ++st)
-          kv[pp][st] = *reinterpret_cast<const u32x4*>(kt + pp * KT + mfma::swz(n, st * 4 + Gq));
+          kv[pp][st] = *reinterpret_cast<const u32x4*>(kt + pp * KT + mfma::swz<D>(n, st * 4 + Gq));
     };
     auto qk = [&](const KOps& kv, f32x4_t (&sc)[kPfBlocks][kPfStep]) {
 #pragma unroll
@@ -306,7 +306,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
           const int d = mb * 16 + 4 * (n & 3);
-          const int off = mfma::swz_v(vkey, d >> 3) + (d & 7) * 2;
+          const int off = mfma::swz_v<D>(vkey, d >> 3) + (d & 7) * 2;
           const s16x4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(vt + off));
           const s16x4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(vt + KT + off));
           const f16x8_t va = __builtin_bit_cast(f16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
@@ -333,7 +333,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
           const int d = mb * 16 + 4 * (n & 3);
-          const int off = mfma::swz_v(vkey, d >> 3) + (d & 7) * 2;
+          const int off = mfma::swz_v<D>(vkey, d >> 3) + (d & 7) * 2;
           const s16x4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(vt + off));
           const s16x4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(vt + KT + off));
           const bf16x8_t va = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));

@@ -26,9 +26,9 @@
 // Per workgroup: prefix sums of page counts over all rows (LDS), then a unit
 // table for its range (page id and flags per unit, LDS), then the units in
 // order, with a workgroup barrier per unit to keep the waves in step.  With
-// the matrix-core fold (bf16, head dim 128) each wave loads a unit's K and V
-// tiles half a unit apart, one register set each; otherwise it runs a ring
-// of NBUF whole-tile register buffers, as the split kernel's inner loop does.
+// the matrix-core fold (bf16) each wave loads a unit's K and V tiles half a unit
+// apart, one register set each; otherwise it runs a ring of NBUF whole-tile
+// register buffers, as the split kernel's inner loop does.
 #include "pa_stream_kernel.h"
 
 namespace pa {

@@ -132,20 +132,20 @@ __device__ __forceinline__ void merge_records(const StreamArgs& a, int x0, int x
 // The record of an item's other part, loaded ahead of merge_held: (M, L) and
 // the unnormalised O of this lane's head column in the matrix-core layout
 // (lanes of heads >= S load nothing).
-template <int S>
+template <int D, int S>
 struct HeldRecord {
   float m = 0.0f, l = 0.0f;
-  f32x4_dev_t o[mfma::kD / 16] = {};
+  f32x4_dev_t o[D / 16] = {};
 };
-template <int S>
-__device__ __forceinline__ void load_held(HeldRecord<S>& r, const float* o, const float* ml, int lane) {
+template <int D, int S>
+__device__ __forceinline__ void load_held(HeldRecord<D, S>& r, const float* o, const float* ml, int lane) {
   asm volatile("" ::: "memory");  // (the loads stay below the look at the counter)
-  const __amdgpu_buffer_rsrc_t rec = record_rsrc(o, S * mfma::kD);
+  const __amdgpu_buffer_rsrc_t rec = record_rsrc(o, S * D);
   const int n = lane & 15, G = lane >> 4;
   if (n < S) {
     load_dev2(ml + n * 2, r.m, r.l);
 #pragma unroll
-    for (int mb = 0; mb < mfma::kD / 16; ++mb) r.o[mb] = load_dev4(rec, mfma::Record<S>::chunk(n, mb, G) * 4);
+    for (int mb = 0; mb < D / 16; ++mb) r.o[mb] = load_dev4(rec, mfma::Record<D, S>::chunk(n, mb, G) * 4);
   }
 }
 
@@ -153,8 +153,8 @@ __device__ __forceinline__ void load_held(HeldRecord<S>& r, const float* o, cons
 // matrix-core state (its record never stored) and whose second part is the
 // record r: the same operations in the same order as merge_records over the two
 // records, so the output bits do not depend on which of the two parts merged.
-template <typename T, int S>
-__device__ __forceinline__ void merge_held(const mfma::State<S>& st, const HeldRecord<S>& r, int lane, T* out) {
+template <typename T, int D, int S>
+__device__ __forceinline__ void merge_held(const mfma::State<D, S>& st, const HeldRecord<D, S>& r, int lane, T* out) {
   const float l0 = mfma::total_l(st);  // (every lane: a cross-lane sum)
   const int n = lane & 15, G = lane >> 4;
   if (n < S) {
@@ -162,10 +162,10 @@ __device__ __forceinline__ void merge_held(const mfma::State<S>& st, const HeldR
     const float c0 = fast_exp2(st.m - M), c1 = fast_exp2(r.m - M);
     const float L = fmaf(r.l, c1, fmaf(l0, c0, 0.0f));
 #pragma unroll
-    for (int mb = 0; mb < mfma::kD / 16; ++mb) {
+    for (int mb = 0; mb < D / 16; ++mb) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        store_out<T>(out + n * mfma::kD + mb * 16 + 4 * G + i,
+        store_out<T>(out + n * D + mb * 16 + 4 * G + i,
                      fmaf(r.o[mb][i], c1, fmaf(st.acc[mb][i], c0, 0.0f)) / L);
     }
   }
@@ -254,7 +254,7 @@ __device__ __forceinline__ int info_row_seq(const int32_t* cum, int R, int nb, i
 }
 
 // LDS of one stream-K workgroup.
-template <int W, bool MF>
+template <int W, int D, bool MF>
 struct StreamSmem {
   int32_t cum[kStreamMaxRows + 1];  // page prefix sums over rows
   uint8_t tail[kStreamMaxRows];     // valid tokens of each row's last page
@@ -264,7 +264,7 @@ struct StreamSmem {
   CutItem cut[2];                   // the items cut by the range's start and by its end (x0 = -1: none)
   int32_t last[2];                  // whether this workgroup's part of each completed its counter
   int32_t held;                     // whether the last item's other part has counted
-  __attribute__((aligned(16))) uint8_t kv[MF ? W : 1][MF ? 2 * mfma::kTile : 16];  // per-wave tile staging
+  __attribute__((aligned(16))) uint8_t kv[MF ? W : 1][MF ? 2 * mfma::kTileBytes<D> : 16];  // per-wave tile staging
 };
 
 // Codes in s_tail for rows without units (a row with units holds 1 .. 16,
@@ -278,7 +278,7 @@ constexpr uint8_t kRowZeros = 0x20, kRowNaN = 0x40;
 // through the ring of NBUF whole tiles (the mixed kernel, whose decode
 // workgroups share HBM with prefill workgroups and need the longer lead).
 template <typename T, int D, int S, int W, int NBUF, bool MF, bool TR = false, bool SPLIT = kStreamSplitKV>
-__device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, MF>& sm, int bid, int G_) {
+__device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, D, MF>& sm, int bid, int G_) {
   using Sh = DecodeShape<T, D, S>;
   constexpr int NT = 64 * W;
   int32_t* s_cum = sm.cum;
@@ -315,8 +315,10 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
   const int U = a.nb * s_cum[R];
   // A batch of fewer units than workgroups runs on the first U of them, one
   // unit each (no range is ever empty).  Ranges of at least two or three units
-  // save parts to merge but stream alone for longer: within 3 % on most small
-  // batches, 35 % slower on 8 sequences of 20 to 60 tokens.
+  // would save parts to merge but stream alone for longer: within 3 % on most
+  // small batches, 35 % slower on 8 sequences of 20 to 60 tokens.  Nor does it
+  // pay to use the fewest ranges that keep the longest one's length: 8 to 12
+  // sequences -13 to +25 %.
   const int G = max(1, min(G_, U));
   // Rows without units: zeros for an empty decode context, NaN for a contract
   // violation (flagged in s_tail above); rows r = bid (mod G) are this
@@ -364,7 +366,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
   const T* qbase = reinterpret_cast<const T*>(a.q);
 
   DecodeState<T, D, S> st;
-  mfma::State<S> ms;  // matrix-core variant (bf16, D = 128)
+  mfma::State<D, S> ms;  // matrix-core variant (bf16)
   auto& s_kv = sm.kv;
   bool head_partial = false;
 
@@ -454,7 +456,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
   // the item ending the range has one other part, which has counted, and
   // its record is in held_rec.
   bool held_now = false;
-  HeldRecord<S> held_rec;
+  HeldRecord<D, S> held_rec;
 
   // Start of unit k, every wave in step (without the barrier the older wave
   // of each SIMD runs ahead, waves 0..3 finish ~30% before waves 4..7, and
@@ -472,7 +474,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
         const int g = info_hb(info) * W + w;
         const T* qg = qbase + ((int64_t)info_row(info) * a.H_q + (int64_t)g * S) * D;
         if constexpr (MF) {
-          mfma::begin_item<S>(ms, reinterpret_cast<const uint16_t*>(qg), lane);
+          mfma::begin_item<D, S>(ms, reinterpret_cast<const uint16_t*>(qg), lane);
         } else {
           const T* qp = qg + dl * Sh::VEC;
 #pragma unroll
@@ -499,20 +501,20 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
       T* outp = reinterpret_cast<T*>(a.out) + ((int64_t)r * a.H_q + (int64_t)g * S) * D;
       if (!head_partial && !tail_partial) {  // the whole item in this range
         if constexpr (MF)
-          mfma::finish<S, T>(ms, lane, outp);
+          mfma::finish<D, S, T>(ms, lane, outp);
         else
           finish_rows<T, D, S>(st, row, dl, outp);
       } else {  // (workgroup-uniform)
         if constexpr (MF) {
           if (held_now && k == n_units - 1) {
-            merge_held<T, S>(ms, held_rec, lane, outp);
+            merge_held<T, D, S>(ms, held_rec, lane, outp);
             if (tid == 0) counter_reset(a.ws_flag + (int64_t)bid * W, a.tag);
             return;
           }
         }
         const int64_t slot = ((int64_t)bid * 2 + (head_partial ? 0 : 1)) * W + w;
         if constexpr (MF)
-          mfma::partial<S>(ms, lane, a.ws_o + slot * S * D, a.ws_ml + slot * S * 2);
+          mfma::partial<D, S>(ms, lane, a.ws_o + slot * S * D, a.ws_ml + slot * S * 2);
         else
           partial_rows<T, D, S>(st, row, dl, lane, a.ws_o + slot * S * D, a.ws_ml + slot * S * 2);
         if (head_partial) job_begin(std::integral_constant<int, 0>{}, r, g);
@@ -533,7 +535,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
         const CutItem cut = sm.cut[j];
         T* outp = reinterpret_cast<T*>(a.out) + ((int64_t)of_job(j, job_row[0], job_row[1]) * a.H_q +
                                                  (int64_t)of_job(j, job_g[0], job_g[1]) * S) * D;
-        using Rec = std::conditional_t<MF, mfma::Record<S>, RowsRecord<D, S>>;
+        using Rec = std::conditional_t<MF, mfma::Record<D, S>, RowsRecord<D, S>>;
         merge_records<T, D, S, W, Rec>(a, cut.x0, cut.first(lv, bid), cut.step(lv), cut.parts(lv, bid), lv == 1, w,
                                        lane, outp);
         // (a group's record counts in the item next)
@@ -567,7 +569,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
       const T* qg = qbase + ((int64_t)info_row(info) * a.H_q + (int64_t)g * S) * D;
       // lane (n, G): row n of the group (zeros past the S rows), dims
       // 32 s + 8 G .. +8 of Q^T operand s
-      asm_issue<mfma::kD / 32, 64>(scalar_rsrc(qg, S * D * 2), (n_q * D + g_q * 8) * 2, ms.qt);
+      asm_issue<D / 32, 64>(scalar_rsrc(qg, S * D * 2), (n_q * D + g_q * 8) * 2, ms.qt);
     };
     auto tile_k = [&](int k, u32x4 (&x)[Sh::NI]) {
       int64_t off;
@@ -614,7 +616,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
       const int info = __builtin_amdgcn_readfirstlane(s_info[k]);
       if (info_start(info) || k == 0) {
         head_partial = !info_start(info);
-        mfma::reset<S>(ms);
+        mfma::reset<D, S>(ms);
       }
       vm_wait<Sh::NI>(kc);  // K of unit k and the queries (issued before it)
       vm_wait<Sh::NI>(ms.qt);
@@ -623,11 +625,11 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
         held_now = sm.held;
         if (held_now) {
           const int64_t slot = ((int64_t)(bid + 1) * 2 + 0) * W + w;
-          load_held<S>(held_rec, a.ws_o + slot * S * D, a.ws_ml + slot * S * 2, lane);
+          load_held<D, S>(held_rec, a.ws_o + slot * S * D, a.ws_ml + slot * S * 2, lane);
         }
       }
       mfma::s16x4_t phi, plo;
-      mfma::fold_qk<S>(ms, kc, s_kv[w], lane, info_valid(info), a.scale_log2, phi, plo);
+      mfma::fold_qk<D, S>(ms, kc, s_kv[w], lane, info_valid(info), a.scale_log2, phi, plo);
       if (k + 1 < n_units) {  // the queries are free once the QK half is done
         const int next = __builtin_amdgcn_readfirstlane(s_info[k + 1]);
         if (info_start(next)) load_queries(next);
@@ -635,7 +637,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
       tile_k(k + 1, kc);
       jobs_stored(std::integral_constant<int, (Sh::NI & 15) | (7 << 4) | (15 << 8)>{});
       vm_wait<Sh::NI>(vc);  // V of unit k
-      mfma::fold_pv<S>(ms, vc, s_kv[w], lane, phi, plo);
+      mfma::fold_pv<D, S>(ms, vc, s_kv[w], lane, phi, plo);
       tile_v(k + 1, vc);
       end_unit(k, info);
       if (held && w == 0 && k + 2 == n_units) look(std::integral_constant<int, 2 * Sh::NI>{});
@@ -660,7 +662,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, M
         jobs_stored(std::integral_constant<int, kWaitRing>{});
         if (k < n_units) {
           if constexpr (MF)
-            mfma::fold<S>(ms, kr[u], vr[u], s_kv[w], lane, info_valid(info), a.scale_log2);
+            mfma::fold<D, S>(ms, kr[u], vr[u], s_kv[w], lane, info_valid(info), a.scale_log2);
           else
             fold_tile<T, D, S>(st, kr[u], vr[u], row, info_valid(info), a.scale_log2);
           end_unit(k, info);

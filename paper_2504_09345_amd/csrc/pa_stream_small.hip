@@ -1,5 +1,5 @@
-// Stream-K decode kernels for bf16 with head_dim 64 and for fp32 (the
-// matrix-core variant covers bf16 with head_dim 128 in pa_stream.hip).
+// Stream-K decode kernels for bf16 with head_dim 64 (matrix-core fold) and for
+// fp32 (VALU fold).
 #include "pa_stream_kernel.h"
 
 namespace pa {

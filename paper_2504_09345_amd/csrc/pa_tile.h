@@ -303,17 +303,19 @@ __device__ __forceinline__ void partial_rows(const DecodeState<T, D, S>& st, int
 
 
 // ---------------------------------------------------------------------------
-// Matrix-core variant of the decode fold (bf16, head_dim 128).
+// Matrix-core variant of the decode fold (bf16, head_dim 64 or 128).  At D = 64
+// (s = 8, batch 128, 512-2048 tokens) the VALU fold took 140 us, 2.5 TB/s,
+// bound by its vector instructions; this one takes 67 us, 5.2 TB/s.
 //
 // The s query heads of a group are the columns of a 16-wide MFMA tile (padded
 // with zero queries), the 16 tokens of a page its rows:
-//   S^T[token][head] = K . Q^T   4 x v_mfma_f32_16x16x32_bf16 (K as the A operand)
-//   O^T[dim][head]  += V^T . P^T 8 x v_mfma_f32_16x16x32_bf16 (P split into bf16
+//   S^T[token][head] = K . Q^T   D / 32 x v_mfma_f32_16x16x32_bf16 (K as the A operand)
+//   O^T[dim][head]  += V^T . P^T D / 16 x v_mfma_f32_16x16x32_bf16 (P split into bf16
 //                                high and low parts for fp32-level accuracy;
 //                                the k dimension holds 4 tokens x {hi, lo})
 // Lane l owns head column l % 16 and tokens 4 (l / 16) .. +3 of every tile, so
 // the softmax state and the rescale stay in the lane.  The wave stages each
-// tile through its own 8 KiB of LDS, K and V with 16-byte chunks XOR-swizzled
+// tile through its own 64 D bytes of LDS, K and V with 16-byte chunks XOR-swizzled
 // by token (conflict-free operand reads), V read back as the
 // transposed PV operand with ds_read_b64_tr_b16 (lane j of a 16-lane group
 // receives element j % 4 of the 8-byte blocks addressed by lanes j / 4 + 4 i).
@@ -325,43 +327,49 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x8_t __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
 
-constexpr int kD = 128;
-constexpr int kTile = kPage * kD * 2;  // 4 KiB
+template <int D> constexpr int kTileBytes = kPage * D * 2;  // 4 KiB at D = 128, 2 KiB at 64
 
-// Byte offset of 16-byte chunk `chunk` of key `key` in a staged [16][kD] bf16
+// Byte offset of 16-byte chunk `chunk` of key `key` in a staged [16][D] bf16
 // tile.  K: chunks XOR-ed with the key, so the 16 lanes of a QK operand read
-// (16 keys, one chunk each) hit 16 distinct bank groups.  V: chunks XOR-ed
-// with 2 (key mod 8), so a transposed PV read (per half wave: 8 keys x 2
-// adjacent chunks) also hits 16 distinct 16-byte bank groups.
-__device__ __forceinline__ int swz(int key, int chunk) { return key * (kD * 2) + ((chunk ^ (key & 15)) << 4); }
-__device__ __forceinline__ int swz_v(int key, int chunk) { return key * (kD * 2) + ((chunk ^ ((key & 7) << 1)) << 4); }
+// (16 keys, one chunk each) hit 16 distinct bank groups.  V: chunks XOR-ed in
+// pairs, so a transposed PV read (per half wave: 8 keys x 2 adjacent chunks)
+// also hits 16 distinct 16-byte bank groups.  At D = 64 two keys share the 256
+// bytes that the banks span, so the XOR-ed number is key / 2.
+template <int D>
+__device__ __forceinline__ int swz(int key, int chunk) {
+  return key * (D * 2) + ((chunk ^ (D == 128 ? key & 15 : key >> 1 & 7)) << 4);
+}
+template <int D>
+__device__ __forceinline__ int swz_v(int key, int chunk) {
+  return key * (D * 2) + ((chunk ^ ((D == 128 ? key & 7 : key >> 1 & 3) << 1)) << 4);
+}
 
-template <int S>
+template <int D, int S>
 struct State {
-  u32x4 qt[kD / 32];   // Q^T operand: head lane%16 (zero when >= s), dims 32 st + 8 (lane/16) .. +8
-  f32x4_t acc[kD / 16];  // O^T: head lane%16, dims 16 mb + 4 (lane/16) + i
+  u32x4 qt[D / 32];   // Q^T operand: head lane%16 (zero when >= s), dims 32 st + 8 (lane/16) .. +8
+  f32x4_t acc[D / 16];  // O^T: head lane%16, dims 16 mb + 4 (lane/16) + i
   float m, l;          // softmax base (log2 units, shared by the 4 lanes of a head) and partial sum
 };
 
 // An item's queries (the Q^T operand), and its fresh softmax state.
-template <int S>
-__device__ __forceinline__ void load_q(State<S>& st, const uint16_t* q_group, int lane) {
+template <int D, int S>
+__device__ __forceinline__ void load_q(State<D, S>& st, const uint16_t* q_group, int lane) {
   const int n = lane & 15, G = lane >> 4;
 #pragma unroll
-  for (int s = 0; s < kD / 32; ++s)
-    st.qt[s] = n < S ? *reinterpret_cast<const u32x4*>(q_group + n * kD + s * 32 + G * 8) : u32x4{0, 0, 0, 0};
+  for (int s = 0; s < D / 32; ++s)
+    st.qt[s] = n < S ? *reinterpret_cast<const u32x4*>(q_group + n * D + s * 32 + G * 8) : u32x4{0, 0, 0, 0};
 }
-template <int S>
-__device__ __forceinline__ void reset(State<S>& st) {
+template <int D, int S>
+__device__ __forceinline__ void reset(State<D, S>& st) {
 #pragma unroll
-  for (int mb = 0; mb < kD / 16; ++mb) st.acc[mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int mb = 0; mb < D / 16; ++mb) st.acc[mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   st.m = kMInit;
   st.l = 0.0f;
 }
-template <int S>
-__device__ __forceinline__ void begin_item(State<S>& st, const uint16_t* q_group, int lane) {
-  load_q<S>(st, q_group, lane);
-  reset<S>(st);
+template <int D, int S>
+__device__ __forceinline__ void begin_item(State<D, S>& st, const uint16_t* q_group, int lane) {
+  load_q<D, S>(st, q_group, lane);
+  reset<D, S>(st);
 }
 
 // Split four fp32 softmax weights into bf16 high parts (round to nearest
@@ -393,23 +401,24 @@ __device__ __forceinline__ f32x4_t pv_mfma(const s16x4_t& va, const s16x4_t& phi
 }
 
 // The fold of one tile in two halves, so that a tile's V loads can be waited
-// for after its K half is done.  k / v: the tile as loaded (lane l: token
-// l/16 + 4 i, 16-byte chunk l%16); lds: this wave's 8 KiB (K then V); valid:
-// live tokens of the tile.
+// for after its K half is done.  k / v: the tile as loaded (lane l: 16-byte
+// chunk l mod D/8 of token l / (D/8) + 512/D i); lds: this wave's staging (K
+// then V); valid: live tokens of the tile.
 //
 // fold_qk: K to LDS, S^T = K . Q^T, online softmax; the P^T operands (bf16
 // high and low parts of the lane's 4 weights) come back in phi / plo.
-template <int S>
-__device__ __forceinline__ void fold_qk(State<S>& st, const u32x4 (&k)[4], uint8_t* lds, int lane, int valid,
+template <int D, int S>
+__device__ __forceinline__ void fold_qk(State<D, S>& st, const u32x4 (&k)[D / 32], uint8_t* lds, int lane, int valid,
                                         float scale_log2, s16x4_t& phi, s16x4_t& plo) {
-  const int G = lane >> 4, p = lane & 15;
+  constexpr int TPI = 512 / D;  // tokens per wave-wide load
+  const int G = lane >> 4, p = lane & 15, tok = lane / (D / 8), chunk = lane % (D / 8);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(lds + swz(G + 4 * i, p)) = k[i];
+  for (int i = 0; i < D / 32; ++i) *reinterpret_cast<u32x4*>(lds + swz<D>(tok + TPI * i, chunk)) = k[i];
   // S^T = K . Q^T
   f32x4_t s = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int step = 0; step < kD / 32; ++step) {
-    const u32x4 ka = *reinterpret_cast<const u32x4*>(lds + swz(p, step * 4 + G));
+  for (int step = 0; step < D / 32; ++step) {
+    const u32x4 ka = *reinterpret_cast<const u32x4*>(lds + swz<D>(p, step * 4 + G));
     s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka), __builtin_bit_cast(bf16x8_t, st.qt[step]),
                                                 s, 0, 0, 0);
   }
@@ -429,7 +438,7 @@ __device__ __forceinline__ void fold_qk(State<S>& st, const u32x4 (&k)[4], uint8
     st.m = mc;
     st.l *= alpha;
 #pragma unroll
-    for (int mb = 0; mb < kD / 16; ++mb) st.acc[mb] *= alpha;
+    for (int mb = 0; mb < D / 16; ++mb) st.acc[mb] *= alpha;
   }
   float pw[4];
 #pragma unroll
@@ -440,50 +449,51 @@ __device__ __forceinline__ void fold_qk(State<S>& st, const u32x4 (&k)[4], uint8
 
 // fold_pv: V to LDS, O^T += V^T . P^T; lane p of group G addresses token
 // 4 G + p / 4, dims 16 mb + 4 (p % 4).
-template <int S>
-__device__ __forceinline__ void fold_pv(State<S>& st, const u32x4 (&v)[4], uint8_t* lds, int lane,
+template <int D, int S>
+__device__ __forceinline__ void fold_pv(State<D, S>& st, const u32x4 (&v)[D / 32], uint8_t* lds, int lane,
                                         const s16x4_t& phi, const s16x4_t& plo) {
-  const int G = lane >> 4, p = lane & 15;
+  constexpr int TPI = 512 / D;  // tokens per wave-wide load
+  const int G = lane >> 4, p = lane & 15, tok = lane / (D / 8), chunk = lane % (D / 8);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(lds + kTile + swz_v(G + 4 * i, p)) = v[i];
+  for (int i = 0; i < D / 32; ++i) *reinterpret_cast<u32x4*>(lds + kTileBytes<D> + swz_v<D>(tok + TPI * i, chunk)) = v[i];
   const int vtok = 4 * G + (p >> 2);
 #pragma unroll
-  for (int mb = 0; mb < kD / 16; ++mb) {
+  for (int mb = 0; mb < D / 16; ++mb) {
     const int d = mb * 16 + 4 * (p & 3);
-    const lds_s16x4_t* src = (const lds_s16x4_t*)(lds + kTile + swz_v(vtok, d >> 3) + (d & 7) * 2);
+    const lds_s16x4_t* src = (const lds_s16x4_t*)(lds + kTileBytes<D> + swz_v<D>(vtok, d >> 3) + (d & 7) * 2);
     const s16x4_t va = __builtin_amdgcn_ds_read_tr16_b64_v4i16(const_cast<lds_s16x4_t*>(src));
     st.acc[mb] = pv_mfma(va, phi, plo, st.acc[mb]);
   }
 }
 
 // Both halves of one tile.
-template <int S>
-__device__ __forceinline__ void fold(State<S>& st, const u32x4 (&k)[4], const u32x4 (&v)[4], uint8_t* lds, int lane,
+template <int D, int S>
+__device__ __forceinline__ void fold(State<D, S>& st, const u32x4 (&k)[D / 32], const u32x4 (&v)[D / 32], uint8_t* lds, int lane,
                                      int valid, float scale_log2) {
   s16x4_t phi, plo;
-  fold_qk<S>(st, k, lds, lane, valid, scale_log2, phi, plo);
-  fold_pv<S>(st, v, lds, lane, phi, plo);
+  fold_qk<D, S>(st, k, lds, lane, valid, scale_log2, phi, plo);
+  fold_pv<D, S>(st, v, lds, lane, phi, plo);
 }
 
 // Totals of the head column of this lane: L summed over the 4 lane groups.
-template <int S>
-__device__ __forceinline__ float total_l(const State<S>& st) {
+template <int D, int S>
+__device__ __forceinline__ float total_l(const State<D, S>& st) {
   return rows4_sum(st.l);
 }
 
 // Finish an item in place: out points at head 0 of the group ([s][D]).
-template <int S, typename T>
-__device__ __forceinline__ void finish(const State<S>& st, int lane, T* out) {
+template <int D, int S, typename T>
+__device__ __forceinline__ void finish(const State<D, S>& st, int lane, T* out) {
   const float L = total_l(st);
   const int n = lane & 15, G = lane >> 4;
   if (n < S) {
     const float inv = 1.0f / L;
 #pragma unroll
-    for (int mb = 0; mb < kD / 16; ++mb) {
+    for (int mb = 0; mb < D / 16; ++mb) {
       const int d = mb * 16 + 4 * G;
       const uint32_t lo = (uint32_t)f32_to_bf16(st.acc[mb][0] * inv) | (uint32_t)f32_to_bf16(st.acc[mb][1] * inv) << 16;
       const uint32_t hi = (uint32_t)f32_to_bf16(st.acc[mb][2] * inv) | (uint32_t)f32_to_bf16(st.acc[mb][3] * inv) << 16;
-      *reinterpret_cast<uint2*>(out + n * kD + d) = make_uint2(lo, hi);
+      *reinterpret_cast<uint2*>(out + n * D + d) = make_uint2(lo, hi);
     }
   }
 }
@@ -491,21 +501,21 @@ __device__ __forceinline__ void finish(const State<S>& st, int lane, T* out) {
 // Partial record: unnormalised O in 16-byte chunks in the accumulators' order
 // (chunk c: head c / 4 mod s, dims 16 (c / 4 s) + 4 (c mod 4) .. +3, so the
 // lanes of one store write adjacent chunks) and (M, L) per head.
-template <int S>
+template <int D, int S>
 struct Record {
   static __device__ __forceinline__ int head(int c) { return c / 4 % S; }
   static __device__ __forceinline__ int dim(int c) { return c / (4 * S) * 16 + c % 4 * 4; }
   // chunk of head n, accumulator mb, lane group G
   static __device__ __forceinline__ int chunk(int n, int mb, int G) { return (mb * S + n) * 4 + G; }
 };
-template <int S>
-__device__ __forceinline__ void partial(const State<S>& st, int lane, float* o, float* ml) {
+template <int D, int S>
+__device__ __forceinline__ void partial(const State<D, S>& st, int lane, float* o, float* ml) {
   const float L = total_l(st);
   const int n = lane & 15, G = lane >> 4;
-  const __amdgpu_buffer_rsrc_t r = record_rsrc(o, S * kD);
+  const __amdgpu_buffer_rsrc_t r = record_rsrc(o, S * D);
   if (n < S) {
 #pragma unroll
-    for (int mb = 0; mb < kD / 16; ++mb) store_dev4(r, Record<S>::chunk(n, mb, G) * 4, st.acc[mb]);
+    for (int mb = 0; mb < D / 16; ++mb) store_dev4(r, Record<D, S>::chunk(n, mb, G) * 4, st.acc[mb]);
     if (G == 0) store_dev(ml + n * 2, st.m, L);
   }
 }

@@ -188,3 +188,23 @@ def test_checker_on_hand_written_paths():
         s_waitcnt vmcnt(0)
         v_mov_b32_e32 v4, 0
         s_endpgm""") == [None]
+
+
+def test_split_loads_at_head_dim_64():
+    """The same check on the head_dim 64 kernels (their tiles are two loads)."""
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("hipcc not available")
+    cmd = [build.HIPCC, *build.FLAGS, "--cuda-device-only", "-S",
+           os.path.join(build.CSRC, "pa_stream_small.hip"), "-o", "-"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    kernels = [k for k in _kernels(r.stdout) if "ItLi64E" in k[0]]
+    assert kernels
+    for name, lines, loads in kernels:
+        assert loads, name
+        labels = {m.group(1): j for j, l in enumerate(lines) if (m := re.match(r"(\.LBB\w+):", l))}
+        for i in sorted(loads):
+            m = re.match(r"\w+ v\[(\d+):(\d+)\]", lines[i])
+            dst = set(range(int(m.group(1)), int(m.group(2)) + 1))
+            t = _untouched(lines, labels, set(loads), i, dst, counted=not lines[i].startswith("global_load"))
+            assert t is None, f"{name}: `{t}` touches {lines[i]!r} before its wait"
