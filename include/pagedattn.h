@@ -147,11 +147,12 @@ int paged_attn(const void *q, const void *k_pages, const void *v_pages,
 
 /* Mixed batch: causal prefill chunks and decode rows in one call.  Decode
  * rows take the stream-K kernel; chunk rows (L_b > 1) take an MFMA kernel
- * (bf16, head_dim 128) or, otherwise, the per-row split-K kernel.  The MFMA
+ * (bf16) or, otherwise, the per-row split-K kernel.  At head_dim 128 the MFMA
  * kernel forms P.V with P rounded to fp16 (relative error 2^-11) and V in
  * fp16 (exact for bf16 magnitudes in [2^-17, 2^16)); a chunk block whose V
  * leaves that range (or holds inf / NaN), or whose output rows have an RMS
- * below 2^-14, is computed again with fp32-level P.V.  When every sequence
+ * below 2^-14, is computed again with fp32-level P.V (P as bf16 high and low
+ * parts), the form that head_dim 64 always takes.  When every sequence
  * has max_q_len > 1 rows, only the chunk kernel runs.
  * Same as paged_attn, with q/out of [num_q_rows][H_q][D] and the device array
  * query_start_loc (see layouts).  Row j of a chunk of length L in a sequence
@@ -175,7 +176,7 @@ int paged_attn_varlen(const void *q, const void *k_pages, const void *v_pages,
  *   - A call that needs more than the 32 MiB returns PA_ENOSPC and enqueues
  *     nothing.  The stream-K decode rows need 66.5 KiB per workgroup of the
  *     grid at s = 8 (33 KiB at s = 4, 208 workgroups on MI355X: ~7 MB);
- *     chunk rows that take the per-row split-K kernel (fp32, head_dim 64)
+ *     fp32 and head_dim 64 chunk rows
  *     need rows x H_q x splits x (D + 2) x 4 bytes.
  *   - Every call on one GPU shares that GPU's array and leaves its contents
  *     behind (a counter is left ready for the next call, and anything else in

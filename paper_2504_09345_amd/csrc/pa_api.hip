@@ -105,7 +105,7 @@ int plan(const pa_dims_t* d, bool varlen, Plan* p) {
     // arrival counters of cut items: one per (first range, wave)
     p->st_cum = align256((size_t)pa::kStreamMaxGrid * p->W * sizeof(unsigned long long));
   }
-  // chunked-prefill rows of a varlen call: MFMA kernel (bf16, head_dim 128)
+  // chunked-prefill rows of a varlen call: MFMA kernel (bf16)
   // (a call with at most one row per sequence has none; its decode rows then
   // take the stream kernel alone, as paged_attn's do, instead of sharing the
   // mixed launch with workgroups that would find no chunk)
@@ -116,10 +116,14 @@ int plan(const pa_dims_t* d, bool varlen, Plan* p) {
   // max_q_len <= 1: every row is then a decode row, which the stream kernel
   // takes)
   p->split = varlen ? (rows > 0 && !p->prefill && (d->max_q_len > 1 || !p->stream)) : !p->stream;
+  // head_dim 64 chunks took the split-K kernel before the MFMA kernel did: the
+  // workspace stays sized (and a call refused) as if they still do, so that
+  // sizes that callers keep, and what fits the fixed scratch, do not change
+  const bool sized_as_split = p->split || (p->prefill && d->head_dim != 128 && d->max_q_len > 1);
   p->pps = d->pages_per_split > 0 ? d->pages_per_split : kDefaultPagesPerSplit;
   p->n_split_slots = (int)((max_pages + p->pps - 1) / p->pps);
   if (p->n_split_slots < 1) p->n_split_slots = 1;
-  if (p->split) {
+  if (sized_as_split) {
     if ((int64_t)rows * d->num_kv_heads * p->n_split_slots > 0x7fffffffLL) return PA_ENOTSUP;
     if (p->n_split_slots > 1) {
       const size_t items = (size_t)rows * (size_t)d->num_q_heads * (size_t)p->n_split_slots;
@@ -350,9 +354,9 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
       const int g_dec = G < cus - g_pf ? G : (cus - g_pf > p.g_min ? cus - g_pf : (int)p.g_min);
       e = pa::launch_mixed(p.s, sa, pf, g_dec, g_dec + g_pf, stream, next_events());
     } else {
-      const int per_cu = pa::prefill_occupancy(p.s, dims->num_seqs);
+      const int per_cu = pa::prefill_occupancy(dims->head_dim, p.s, dims->num_seqs);
       if (per_cu <= 0) return PA_EHIP;
-      e = pa::launch_prefill(p.s, pf, per_cu * cus, stream, next_events());
+      e = pa::launch_prefill(dims->head_dim, p.s, pf, per_cu * cus, stream, next_events());
     }
     if (e != hipSuccess) return PA_EHIP;
   }

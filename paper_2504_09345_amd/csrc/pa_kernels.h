@@ -110,7 +110,7 @@ int stream_occupancy(int dtype, int D, int s, int W);  // workgroups per CU, 0 o
 // translation unit per combination, compiled in parallel).
 template <typename T, int D, bool TR> const void* stream_pick(int s, int W);
 
-// Arguments of the MFMA chunked-prefill kernel (bf16, head_dim 128): the rows
+// Arguments of the MFMA chunked-prefill kernel (bf16): the rows
 // of every sequence with a chunk of L > 1 query rows.
 struct PrefillArgs {
   const void* q;
@@ -133,8 +133,8 @@ bool prefill_supported(int dtype, int D, int s);
 bool mixed_supported(int dtype, int D, int s, int W);
 hipError_t launch_mixed(int s, const StreamArgs& sa, const PrefillArgs& pa, int G_dec, int G, hipStream_t st,
                         KernelEvents ev = {});
-int prefill_occupancy(int s, int B);  // workgroups per CU, 0 on error
-hipError_t launch_prefill(int s, const PrefillArgs& a, int G, hipStream_t st, KernelEvents ev = {});
+int prefill_occupancy(int D, int s, int B);  // workgroups per CU, 0 on error
+hipError_t launch_prefill(int D, int s, const PrefillArgs& a, int G, hipStream_t st, KernelEvents ev = {});
 
 // Arguments of the KV-append (cache write) kernel.  query_start_loc == nullptr
 // is the decode layout (row b appends position context_lens[b] - 1).

@@ -27,6 +27,15 @@
 // loaded, P as its bf16 high and low parts in two v_mfma_f32_16x16x32_bf16
 // (fp32-level accuracy).  Both conditions are read off the first pass's
 // output rows.
+// head_dim 64 takes the bf16 form only (its chunks ran with fp32 weights on the
+// split-K kernel before, and fp16 P would lose precision against that), four
+// pages per step, so that a step stages the same bytes and keeps as many
+// products between barriers; an item with a row that is not finite is computed
+// again row by row, so that a V that is infinite or NaN reaches only the rows
+// that see its key.  Bound by the matrix products and the softmax's vector
+// instructions like head_dim 128: 4 chunks of 200-400 rows on 0-1024 tokens
+// 177 -> 46 us (145 TFLOP/s), 8 of 512 rows 909 -> 107 us (351 TFLOP/s), 8 of
+// 2,048 rows 10.6 ms -> 0.48 ms (535 TFLOP/s).
 // Computing the transposed products keeps "lane l % 16 = query row" in every
 // accumulator, so the softmax statistics, the P operand and the O rescale all
 // stay in the lane that owns the row: no register transposes.
@@ -52,25 +61,29 @@ __global__ __launch_bounds__(kPfThreads) void prefill_kernel(PrefillArgs a) {
   prefill_body<D, S, TR>(a, sm, s_cum, blockIdx.x, gridDim.x);
 }
 
-template <bool TR>
+template <int D, bool TR>
 static const void* prefill_pick(int s) {
   switch (s) {
-    case 1: return reinterpret_cast<const void*>(&prefill_kernel<128, 1, TR>);
-    case 2: return reinterpret_cast<const void*>(&prefill_kernel<128, 2, TR>);
-    case 4: return reinterpret_cast<const void*>(&prefill_kernel<128, 4, TR>);
-    case 6: return reinterpret_cast<const void*>(&prefill_kernel<128, 6, TR>);
-    case 8: return reinterpret_cast<const void*>(&prefill_kernel<128, 8, TR>);
+    case 1: return reinterpret_cast<const void*>(&prefill_kernel<D, 1, TR>);
+    case 2: return reinterpret_cast<const void*>(&prefill_kernel<D, 2, TR>);
+    case 4: return reinterpret_cast<const void*>(&prefill_kernel<D, 4, TR>);
+    case 6: return reinterpret_cast<const void*>(&prefill_kernel<D, 6, TR>);
+    case 8: return reinterpret_cast<const void*>(&prefill_kernel<D, 8, TR>);
   }
   return nullptr;
 }
 
 // trace: the gather-trace instantiation (also records the rows it loads)
-static const void* prefill_fn(int s, bool trace = false) { return trace ? prefill_pick<true>(s) : prefill_pick<false>(s); }
+static const void* prefill_fn(int D, int s, bool trace = false) {
+  if (D == 128) return trace ? prefill_pick<128, true>(s) : prefill_pick<128, false>(s);
+  if (D == 64) return trace ? prefill_pick<64, true>(s) : prefill_pick<64, false>(s);
+  return nullptr;
+}
 
-bool prefill_supported(int dtype, int D, int s) { return dtype == 0 && D == 128 && prefill_fn(s) != nullptr; }
+bool prefill_supported(int dtype, int D, int s) { return dtype == 0 && prefill_fn(D, s) != nullptr; }
 
-int prefill_occupancy(int s, int B) {
-  const void* fn = prefill_fn(s);
+int prefill_occupancy(int D, int s, int B) {
+  const void* fn = prefill_fn(D, s);
   if (fn == nullptr) return 0;
   int n = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, kPfThreads, (size_t)(B + 1) * sizeof(int32_t)) != hipSuccess)
@@ -78,8 +91,8 @@ int prefill_occupancy(int s, int B) {
   return n;
 }
 
-hipError_t launch_prefill(int s, const PrefillArgs& a, int G, hipStream_t st, KernelEvents ev) {
-  const void* fn = prefill_fn(s, a.trace != nullptr);
+hipError_t launch_prefill(int D, int s, const PrefillArgs& a, int G, hipStream_t st, KernelEvents ev) {
+  const void* fn = prefill_fn(D, s, a.trace != nullptr);
   if (fn == nullptr || G <= 0) return hipErrorInvalidValue;
   void* args[] = {const_cast<PrefillArgs*>(&a)};
   hipError_t e = hipExtLaunchKernel(fn, dim3(G), dim3(kPfThreads), args, (size_t)(a.B + 1) * sizeof(int32_t), st,

@@ -23,7 +23,8 @@ constexpr int kPfThreads = 64 * kPfWaves;
 constexpr int kPfBlocks = 2;                       // 16-row MFMA blocks per wave
 constexpr int kPfRows = 16 * kPfBlocks * kPfWaves;  // 256 query rows per item
 constexpr int kPfMaxPages = 2048;                  // block-table window in LDS (power of 2)
-constexpr int kPfStep = 2;                         // pages per synchronised step
+constexpr int kPfStepBytes = 8192;                 // K (and V) bytes of a synchronised step
+template <int D> constexpr int kPfStep = kPfStepBytes / (kPage * D * 2);  // its pages: 2 at D = 128, 4 at 64
 constexpr int kPfLdsSteps = 3;                     // steps staged in LDS at once
 // Cache policy of the prefill K/V loads: the default (cached).  The items of
 // one (sequence, KV head) re-read the same causal prefix of pages, so cached
@@ -33,8 +34,8 @@ constexpr int kPfLoadPolicy = 0;
 
 // LDS of one prefill workgroup (besides the per-sequence item prefix sums).
 struct PrefillSmem {
-  __attribute__((aligned(16))) uint8_t k[kPfLdsSteps][kPfStep * kPage * 128 * 2];
-  __attribute__((aligned(16))) uint8_t v[kPfLdsSteps][kPfStep * kPage * 128 * 2];
+  __attribute__((aligned(16))) uint8_t k[kPfLdsSteps][kPfStepBytes];
+  __attribute__((aligned(16))) uint8_t v[kPfLdsSteps][kPfStepBytes];
   int32_t bt[kPfMaxPages];
   int32_t scan[kPfThreads];
   int32_t vwide;  // the item needs the bf16 pass (non-finite or tiny output rows after the fp16 pass)
@@ -46,7 +47,10 @@ struct PrefillSmem {
 template <int D, int S, bool TR = false>
 __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& sm, int32_t* s_cum, int bid,
                                              int G) {
-  static_assert(D == 128, "prefill MFMA path is built for head_dim 128");
+  // V and P in fp16 (one product) with a bf16 pass where that does not hold, or
+  // only the bf16 pass
+  constexpr bool kF16 = D == 128;
+  constexpr int kPfStep = pa::kPfStep<D>;
   constexpr int PB = kPfRows / S;       // chunk positions per item
   constexpr int KSTEPS = D / 32;        // QK MFMA steps over dims
   constexpr int MB = D / 16;            // PV MFMA blocks over dims
@@ -54,7 +58,6 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
   constexpr int C16 = D / 8;            // 16-byte chunks per key
   static_assert(kPfStep * kPage * C16 == kPfThreads, "one 16-byte chunk of K and V per thread and step");
 
-  static_assert(sizeof(sm.k[0]) == kPfStep * KT, "LDS step size");
   auto& s_k = sm.k;
   auto& s_v = sm.v;
   int32_t* s_bt = sm.bt;
@@ -293,6 +296,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
       const int vkey = 4 * Gq + (n >> 2);
       if constexpr (F16) {
         // fp16 P (nearest even, relative error <= 2^-11) and fp16 V: one product
+        static_assert(!F16 || kPfStep == 2, "the fp16 pass takes one pair of pages per step");
         f16x8_t ph[kPfBlocks];
 #pragma unroll
         for (int rb = 0; rb < kPfBlocks; ++rb) {
@@ -315,32 +319,36 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
             acc[rb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va, ph[rb], acc[rb][mb], 0, 0, 0);
         }
       } else {
-        // bf16 V and P's bf16 high and low parts: two products
-        bf16x8_t phi[kPfBlocks], plo[kPfBlocks];
+        // bf16 V and P's bf16 high and low parts: two products per pair of pages
 #pragma unroll
-        for (int rb = 0; rb < kPfBlocks; ++rb) {
-          s16x4_t h[kPfStep], l[kPfStep];
-#pragma unroll
-          for (int pp = 0; pp < kPfStep; ++pp) {
-            const float q4[4] = {pw[rb][pp * 4], pw[rb][pp * 4 + 1], pw[rb][pp * 4 + 2], pw[rb][pp * 4 + 3]};
-            mfma::split_hi_lo(q4, h[pp], l[pp]);
-          }
-          phi[rb] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7));
-          plo[rb] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(l[0], l[1], 0, 1, 2, 3, 4, 5, 6, 7));
-          acc_l[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, phi[rb], acc_l[rb], 0, 0, 0);
-          acc_l[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, plo[rb], acc_l[rb], 0, 0, 0);
-        }
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          const int d = mb * 16 + 4 * (n & 3);
-          const int off = mfma::swz_v<D>(vkey, d >> 3) + (d & 7) * 2;
-          const s16x4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(vt + off));
-          const s16x4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(vt + KT + off));
-          const bf16x8_t va = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+        for (int pr = 0; pr < kPfStep; pr += 2) {
+          bf16x8_t phi[kPfBlocks], plo[kPfBlocks];
 #pragma unroll
           for (int rb = 0; rb < kPfBlocks; ++rb) {
-            acc[rb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, phi[rb], acc[rb][mb], 0, 0, 0);
-            acc[rb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, plo[rb], acc[rb][mb], 0, 0, 0);
+            s16x4_t h[2], l[2];
+#pragma unroll
+            for (int pp = 0; pp < 2; ++pp) {
+              const float* w4 = pw[rb] + (pr + pp) * 4;
+              const float q4[4] = {w4[0], w4[1], w4[2], w4[3]};
+              mfma::split_hi_lo(q4, h[pp], l[pp]);
+            }
+            phi[rb] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7));
+            plo[rb] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(l[0], l[1], 0, 1, 2, 3, 4, 5, 6, 7));
+            acc_l[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, phi[rb], acc_l[rb], 0, 0, 0);
+            acc_l[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, plo[rb], acc_l[rb], 0, 0, 0);
+          }
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) {
+            const int d = mb * 16 + 4 * (n & 3);
+            const int off = pr * KT + mfma::swz_v<D>(vkey, d >> 3) + (d & 7) * 2;
+            const s16x4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(vt + off));
+            const s16x4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(vt + KT + off));
+            const bf16x8_t va = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+            for (int rb = 0; rb < kPfBlocks; ++rb) {
+              acc[rb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, phi[rb], acc[rb][mb], 0, 0, 0);
+              acc[rb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, plo[rb], acc[rb][mb], 0, 0, 0);
+            }
           }
         }
       }
@@ -428,16 +436,64 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
         if (__builtin_amdgcn_ballot_w64(redo) != 0 && lane == 0) sm.vwide = 1;
       }
     };
-    // fp16 pass; an item whose V does not fit fp16 (or whose output rows are
-    // too small for fp16's subnormal V) is recomputed in bf16
-    pipeline(PfBool<true>{});
-    __syncthreads();  // every wave's check of the pass has set or left the flag
-    if (sm.vwide) {
-      if (npg > kPfMaxPages) {  // the pass slid the block-table window: back to page 0
-        for (int i = tid; i < kPfMaxPages; i += kPfThreads) s_bt[i] = bt.page(b, i);
-        __syncthreads();
+    if constexpr (kF16) {
+      // fp16 pass; an item whose V does not fit fp16 (or whose output rows are
+      // too small for fp16's subnormal V) is recomputed in bf16
+      pipeline(PfBool<true>{});
+      __syncthreads();  // every wave's check of the pass has set or left the flag
+      if (sm.vwide) {
+        if (npg > kPfMaxPages) {  // the pass slid the block-table window: back to page 0
+          for (int i = tid; i < kPfMaxPages; i += kPfThreads) s_bt[i] = bt.page(b, i);
+          __syncthreads();
+        }
+        pipeline(PfBool<false>{});
       }
+    } else {
       pipeline(PfBool<false>{});
+      // A key that a row does not see has weight 0, and where its V is infinite
+      // or NaN the product makes the row NaN: an item with a row that is not
+      // finite is computed again row by row, each over its own keys only (the
+      // split-K kernel's arithmetic; a wave takes every eighth position).
+      bool odd = false;
+#pragma unroll
+      for (int rb = 0; rb < kPfBlocks; ++rb) {
+        const float inv = 1.0f / acc_l[rb][0];
+        float mx = 0.0f;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) mx = fmaxf(mx, __builtin_isfinite(acc[rb][mb][i] * inv) ? 0.0f : 1.0f);
+        odd |= lim[rb] >= 0 && mx > 0.0f;
+      }
+      if (__builtin_amdgcn_ballot_w64(odd) != 0 && lane == 0) sm.vwide = 1;
+      __syncthreads();
+      if (sm.vwide) {
+        using Sh = DecodeShape<uint16_t, D, S>;
+        const int dl = lane % Sh::LPT, row = lane / Sh::LPT;
+        for (int p = w; p < npos; p += kPfWaves) {
+          DecodeState<uint16_t, D, S> st;
+          const int64_t at = ((int64_t)(q0 + pos0 + p) * a.H_q + (int64_t)g * S) * D;
+#pragma unroll
+          for (int j = 0; j < S; ++j) {
+            st.q[j] = *reinterpret_cast<const u32x4*>(qg + at + j * D + dl * Sh::VEC);
+            st.m[j] = kMInit;
+            st.l[j] = 0.0f;
+#pragma unroll
+            for (int e = 0; e < Sh::VEC; ++e) st.o[j][e] = 0.0f;
+          }
+          const int keys = lim0 + p + 1;
+          for (int pg = 0; pg * kPage < keys; ++pg) {
+            const int64_t tile = tile_offset(__builtin_amdgcn_readfirstlane(bt.page(b, pg)), g, a.H_kv, D);
+            const int valid = min(kPage, keys - pg * kPage);
+            u32x4 kr[Sh::NI], vr[Sh::NI];
+            issue_tile<Sh::NI>(tile_rsrc<uint16_t, D>(kp + tile, valid), tile_rsrc<uint16_t, D>(vp + tile, valid),
+                               lane * 16, kr, vr);
+            fold_tile<uint16_t, D, S>(st, kr, vr, row, valid, a.scale_log2);
+          }
+          finish_rows<uint16_t, D, S>(st, row, dl, og + at);
+        }
+        continue;
+      }
     }
 
     // normalise and store straight from the accumulators: lane (n, Gq) holds
