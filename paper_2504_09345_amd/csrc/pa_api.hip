@@ -43,6 +43,7 @@ struct Plan {
   // stream-K path (decode rows)
   bool stream = false;
   int W = 0, nb = 0;
+  int64_t u_max = 0;  // bound on the batch's units
   int64_t g_min = 0;  // persistent workgroups needed to keep every range within the LDS unit table
   size_t st_o = 0, st_ml = 0, st_cum = 0;
   // MFMA prefill path (chunk rows of a varlen call)
@@ -93,8 +94,8 @@ int plan(const pa_dims_t* d, bool varlen, Plan* p) {
          : (d->num_kv_heads % 4 == 0 && pa::kStreamMaxWaves >= 4) ? 4
          : (d->num_kv_heads % 2 == 0 && pa::kStreamMaxWaves >= 2) ? 2 : 1;
   p->nb = d->num_kv_heads / p->W;
-  const int64_t u_max = (int64_t)p->nb * d->num_seqs * max_pages;
-  p->g_min = (u_max + pa::kStreamMaxUnits - 1) / pa::kStreamMaxUnits;
+  p->u_max = (int64_t)p->nb * d->num_seqs * max_pages;
+  p->g_min = (p->u_max + pa::kStreamMaxUnits - 1) / pa::kStreamMaxUnits;
   // an explicit split granule asks for the split-K path
   p->stream = d->pages_per_split == 0 && d->num_seqs <= pa::kStreamMaxRows && p->nb < 64 &&
               rows < (1 << 19) && p->g_min <= pa::kStreamMaxGrid;
@@ -232,14 +233,12 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
   char* ws = static_cast<char*>(workspace);
   hipError_t e = hipSuccess;
   pa::StreamArgs sa{};
-  int G = 0;
+  int G = 0, sub = 1;  // workgroups, and ranges of each
   if (p.stream) {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
       return PA_EHIP;
-    const int per_cu = pa::stream_occupancy(dims->dtype, dims->head_dim, p.s, p.W);
-    if (per_cu <= 0) return PA_EHIP;
     // 13/16 of the CUs (208 of 256 on MI355X, 26 per XCD) stream faster than
     // all of them: fewer requests in flight keep HBM in its efficient range.
     // Back-to-back launches (measured as a sustained loop, MI355X): Mixtral
@@ -258,17 +257,34 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
     // the split-K partials (a caller's workspace, sized for kStreamMaxGrid
     // ranges, always holds it; the fixed scratch may hold the smaller grid
     // only).
+    // With fewer than 8 waves per head block, a workgroup holds several teams
+    // with a range each, unless the batch's ranges would overflow the teams'
+    // smaller unit tables: one KV head of 8 query heads at batch 256, 1k-4k
+    // tokens 69 us against 104 with one team; 2 KV heads of one query head,
+    // head_dim 64, batch 276 59 against 84; 4 KV heads, batch 128 66 against 80.
     const bool all_cus = dims->dtype != PA_BF16 || dims->head_dim != 128 || p.W < 8;
-    for (const bool all : {all_cus, false}) {
-      int64_t g = (int64_t)per_cu * cus * (all ? 1 : kStreamCuNum) / (all ? 1 : kStreamCuDen);
+    const int teams = pa::stream_teams(p.W);
+    const int64_t g_min_teams = (p.u_max + pa::kStreamMaxUnits / teams - 1) / (pa::kStreamMaxUnits / teams);
+    struct Choice {
+      int sub;
+      bool all;
+    };
+    for (const Choice c : {Choice{teams, all_cus}, Choice{1, all_cus}, Choice{1, false}}) {
+      const int64_t least = c.sub > 1 ? (g_min_teams + c.sub - 1) / c.sub : p.g_min;  // workgroups
+      const int64_t most = pa::kStreamMaxGrid / c.sub;
+      if (c.sub > 1 && least > most) continue;
+      const int per_cu = pa::stream_occupancy(dims->dtype, dims->head_dim, p.s, p.W, c.sub);
+      if (per_cu <= 0) return PA_EHIP;
+      int64_t g = (int64_t)per_cu * cus * (c.all ? 1 : kStreamCuNum) / (c.all ? 1 : kStreamCuDen);
       if (g < 1) g = 1;
-      if (g < p.g_min) g = p.g_min;
-      if (g > pa::kStreamMaxGrid) g = pa::kStreamMaxGrid;
+      if (g < least) g = least;
+      if (g > most) g = most;
       G = (int)g;
-      const size_t recs = (size_t)G * 2 * p.W * p.s;
+      sub = c.sub;
+      const size_t recs = (size_t)G * sub * 2 * p.W * p.s;
       p.st_o = align256(recs * (size_t)dims->head_dim * sizeof(float));
       p.st_ml = align256(recs * 2 * sizeof(float));
-      p.st_cum = align256((size_t)G * p.W * sizeof(unsigned long long));
+      p.st_cum = align256((size_t)G * sub * p.W * sizeof(unsigned long long));
       if (p.st_o + p.st_ml + p.st_cum + p.sp_o + p.sp_ml <= workspace_bytes) break;
     }
     sa.q = q;
@@ -322,7 +338,7 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
     return k;
   };
   if (launch_stream && !mixed) {
-    e = pa::launch_stream(dims->dtype, dims->head_dim, p.s, p.W, sa, G, stream, next_events());
+    e = pa::launch_stream(dims->dtype, dims->head_dim, p.s, p.W, sub, sa, G, stream, next_events());
     if (e != hipSuccess) return PA_EHIP;
   }
   if (p.prefill) {

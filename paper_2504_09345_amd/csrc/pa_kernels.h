@@ -74,8 +74,8 @@ struct StreamArgs {
 };
 
 constexpr int kStreamMaxRows = 8192;    // sequences per call on the stream path
-constexpr int kStreamMaxUnits = 2048;   // units per workgroup range (LDS unit table)
-constexpr int kStreamMaxGrid = 1024;    // persistent workgroups (partial-record space)
+constexpr int kStreamMaxUnits = 2048;   // units of a workgroup's ranges (LDS unit tables)
+constexpr int kStreamMaxGrid = 1024;    // ranges (partial-record space)
 #ifndef PA_STREAM_RING
 #define PA_STREAM_RING 2
 #endif
@@ -103,12 +103,17 @@ struct KernelEvents {
   hipEvent_t start = nullptr, stop = nullptr;
 };
 
-hipError_t launch_stream(int dtype, int D, int s, int W, const StreamArgs& a, int G, hipStream_t st,
+// Teams of W waves per stream-K workgroup where W < 8 (a range each): 8 waves
+// per CU keep HBM busy where one team would not.  With one KV head 4 teams, so
+// that the ranges of every CU fit kStreamMaxGrid.
+constexpr int stream_teams(int W) { return W == 1 ? 4 : 8 / W; }
+// sub: 1 or stream_teams(W); G: workgroups (of sub ranges each).
+hipError_t launch_stream(int dtype, int D, int s, int W, int sub, const StreamArgs& a, int G, hipStream_t st,
                          KernelEvents ev = {});
-int stream_occupancy(int dtype, int D, int s, int W);  // workgroups per CU, 0 on error
+int stream_occupancy(int dtype, int D, int s, int W, int sub);  // workgroups per CU, 0 on error
 // Stream-K kernel for (element type, head dim, trace): pick by s and W (one
 // translation unit per combination, compiled in parallel).
-template <typename T, int D, bool TR> const void* stream_pick(int s, int W);
+template <typename T, int D, bool TR> const void* stream_pick(int s, int W, int sub);
 
 // Arguments of the MFMA chunked-prefill kernel (bf16): the rows
 // of every sequence with a chunk of L > 1 query rows.

@@ -24,7 +24,7 @@ constexpr int kMixedW = 8;  // decode waves per workgroup = prefill waves
 static_assert(64 * kMixedW == kPfThreads, "decode and prefill workgroups must match");
 
 union MixedSmem {
-  StreamSmem<kMixedW, kMixedD, true> dec;
+  StreamSmem<kMixedW, 1, kMixedD, true> dec;
   struct {
     PrefillSmem smem;
     int32_t cum[kStreamMaxRows + 1];
@@ -35,7 +35,7 @@ template <int S, bool TR>
 __global__ __launch_bounds__(64 * kMixedW) void mixed_kernel(StreamArgs sa, PrefillArgs pa_, int G_dec) {
   __shared__ MixedSmem sm;
   if ((int)blockIdx.x < G_dec)
-    stream_body<uint16_t, kMixedD, S, kMixedW, kStreamRing, true, TR, false>(sa, sm.dec, blockIdx.x, G_dec);
+    stream_body<uint16_t, kMixedD, S, kMixedW, 1, kStreamRing, true, TR, false>(sa, sm.dec, blockIdx.x, G_dec);
   else
     prefill_body<kMixedD, S, TR>(pa_, sm.pf.smem, sm.pf.cum, blockIdx.x - G_dec, gridDim.x - G_dec);
 }

@@ -35,38 +35,38 @@ namespace pa {
 
 // Kernels of the other (element type, head dim) combinations and the trace
 // instantiations are compiled in their own translation units.
-extern template const void* stream_pick<uint16_t, 64, false>(int, int);
-extern template const void* stream_pick<float, 128, false>(int, int);
-extern template const void* stream_pick<float, 64, false>(int, int);
-extern template const void* stream_pick<uint16_t, 128, true>(int, int);
-extern template const void* stream_pick<uint16_t, 64, true>(int, int);
-extern template const void* stream_pick<float, 128, true>(int, int);
-extern template const void* stream_pick<float, 64, true>(int, int);
-template const void* stream_pick<uint16_t, 128, false>(int, int);
+extern template const void* stream_pick<uint16_t, 64, false>(int, int, int);
+extern template const void* stream_pick<float, 128, false>(int, int, int);
+extern template const void* stream_pick<float, 64, false>(int, int, int);
+extern template const void* stream_pick<uint16_t, 128, true>(int, int, int);
+extern template const void* stream_pick<uint16_t, 64, true>(int, int, int);
+extern template const void* stream_pick<float, 128, true>(int, int, int);
+extern template const void* stream_pick<float, 64, true>(int, int, int);
+template const void* stream_pick<uint16_t, 128, false>(int, int, int);
 
-static const void* stream_kernel_fn(int dtype, int D, int s, int W, bool trace) {
-  if (dtype == 0 && D == 128) return trace ? stream_pick<uint16_t, 128, true>(s, W) : stream_pick<uint16_t, 128, false>(s, W);
-  if (dtype == 0 && D == 64) return trace ? stream_pick<uint16_t, 64, true>(s, W) : stream_pick<uint16_t, 64, false>(s, W);
-  if (dtype == 1 && D == 128) return trace ? stream_pick<float, 128, true>(s, W) : stream_pick<float, 128, false>(s, W);
-  if (dtype == 1 && D == 64) return trace ? stream_pick<float, 64, true>(s, W) : stream_pick<float, 64, false>(s, W);
+static const void* stream_kernel_fn(int dtype, int D, int s, int W, int sub, bool trace) {
+  if (dtype == 0 && D == 128) return trace ? stream_pick<uint16_t, 128, true>(s, W, sub) : stream_pick<uint16_t, 128, false>(s, W, sub);
+  if (dtype == 0 && D == 64) return trace ? stream_pick<uint16_t, 64, true>(s, W, sub) : stream_pick<uint16_t, 64, false>(s, W, sub);
+  if (dtype == 1 && D == 128) return trace ? stream_pick<float, 128, true>(s, W, sub) : stream_pick<float, 128, false>(s, W, sub);
+  if (dtype == 1 && D == 64) return trace ? stream_pick<float, 64, true>(s, W, sub) : stream_pick<float, 64, false>(s, W, sub);
   return nullptr;
 }
 
-hipError_t launch_stream(int dtype, int D, int s, int W, const StreamArgs& a, int G, hipStream_t st,
+hipError_t launch_stream(int dtype, int D, int s, int W, int sub, const StreamArgs& a, int G, hipStream_t st,
                          KernelEvents ev) {
-  const void* fn = stream_kernel_fn(dtype, D, s, W, a.trace != nullptr);
+  const void* fn = stream_kernel_fn(dtype, D, s, W, sub, a.trace != nullptr);
   if (fn == nullptr || G <= 0) return hipErrorInvalidValue;
   void* args[] = {const_cast<StreamArgs*>(&a)};
-  hipError_t e = hipExtLaunchKernel(fn, dim3(G), dim3(64 * W), args, 0, st, ev.start, ev.stop, 0);
+  hipError_t e = hipExtLaunchKernel(fn, dim3(G), dim3(64 * W * sub), args, 0, st, ev.start, ev.stop, 0);
   if (e != hipSuccess) return e;
   return hipGetLastError();
 }
 
-int stream_occupancy(int dtype, int D, int s, int W) {
-  const void* fn = stream_kernel_fn(dtype, D, s, W, false);
+int stream_occupancy(int dtype, int D, int s, int W, int sub) {
+  const void* fn = stream_kernel_fn(dtype, D, s, W, sub, false);
   if (fn == nullptr) return 0;
   int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, 64 * W, 0) != hipSuccess) return 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, 64 * W * sub, 0) != hipSuccess) return 0;
   return n;
 }
 

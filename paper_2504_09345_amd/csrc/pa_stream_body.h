@@ -253,41 +253,53 @@ __device__ __forceinline__ int info_row_seq(const int32_t* cum, int R, int nb, i
   return lo;
 }
 
-// LDS of one stream-K workgroup.
-template <int W, int D, bool MF>
+// LDS of one stream-K workgroup of SUB teams of W waves.
+template <int W, int SUB, int D, bool MF>
 struct StreamSmem {
+  static constexpr int kTeamUnits = kStreamMaxUnits / SUB;
   int32_t cum[kStreamMaxRows + 1];  // page prefix sums over rows
   uint8_t tail[kStreamMaxRows];     // valid tokens of each row's last page
-  int32_t page[kStreamMaxUnits];    // unit table of the range: page id
-  int32_t info[kStreamMaxUnits];    //   and info word
-  int32_t scan[64 * W];
-  CutItem cut[2];                   // the items cut by the range's start and by its end (x0 = -1: none)
-  int32_t last[2];                  // whether this workgroup's part of each completed its counter
-  int32_t held;                     // whether the last item's other part has counted
-  __attribute__((aligned(16))) uint8_t kv[MF ? W : 1][MF ? 2 * mfma::kTileBytes<D> : 16];  // per-wave tile staging
+  int32_t scan[64 * W * SUB];
+  struct Team {
+    int32_t page[kTeamUnits];  // unit table of the range: page id
+    int32_t info[kTeamUnits];  //   and info word
+    CutItem cut[2];            // the items cut by the range's start and by its end (x0 = -1: none)
+    int32_t last[2];           // whether this team's part of each completed its counter
+    int32_t held;              // whether the last item's other part has counted
+  } team[SUB];
+  __attribute__((aligned(16))) uint8_t kv[MF ? W * SUB : 1][MF ? 2 * mfma::kTileBytes<D> : 16];  // per-wave tile staging
 };
 
 // Codes in s_tail for rows without units (a row with units holds 1 .. 16,
 // the tokens in its last page).
 constexpr uint8_t kRowZeros = 0x20, kRowNaN = 0x40;
 
-// The stream-K decode workgroup `bid` of a grid of G (see pa_stream.hip).
+// The stream-K decode workgroup `wg` of a grid of n_wg (see pa_stream.hip): SUB
+// teams of W waves (a wave per KV head of a head block), each streaming a range
+// of its own in step with the others; range x is team x / n_wg of workgroup
+// x mod n_wg, so a small batch spreads over the workgroups first.  Teams only
+// share the workgroup's barriers and its prefix sums.
 // TR: gather-trace instantiation (records every loaded token's pool row in
 // a.trace besides computing the attention).  SPLIT: with the matrix-core
 // fold, load K and V half a unit apart (the decode-only kernel); without it,
 // through the ring of NBUF whole tiles (the mixed kernel, whose decode
 // workgroups share HBM with prefill workgroups and need the longer lead).
-template <typename T, int D, int S, int W, int NBUF, bool MF, bool TR = false, bool SPLIT = kStreamSplitKV>
-__device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, D, MF>& sm, int bid, int G_) {
+template <typename T, int D, int S, int W, int SUB, int NBUF, bool MF, bool TR = false, bool SPLIT = kStreamSplitKV>
+__device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, SUB, D, MF>& sm, int wg, int n_wg) {
   using Sh = DecodeShape<T, D, S>;
-  constexpr int NT = 64 * W;
+  constexpr int NT = 64 * W * SUB;
   int32_t* s_cum = sm.cum;
   uint8_t* s_tail = sm.tail;
-  int32_t* s_page = sm.page;
-  int32_t* s_info = sm.info;
   int32_t* s_scan = sm.scan;
 
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int team = SUB == 1 ? 0 : wave / W;
+  const int w = SUB == 1 ? wave : wave % W;  // the wave's KV head in a head block
+  const int bid = team * n_wg + wg;          // the team's range
+  auto& tm = sm.team[team];
+  int32_t* s_page = tm.page;
+  int32_t* s_info = tm.info;
   const int R = a.B;  // items are sequences
 
   // 1. pages per sequence and their prefix sums (every workgroup, redundantly)
@@ -319,11 +331,16 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, D
   // small batches, 35 % slower on 8 sequences of 20 to 60 tokens.  Nor does it
   // pay to use the fewest ranges that keep the longest one's length: 8 to 12
   // sequences -13 to +25 %.
-  const int G = max(1, min(G_, U));
+  // Teams beyond the first of each workgroup join once a range has kTeamUnits
+  // units: without that bound 8 sequences with 4 KV heads took 33 us against
+  // 25 (more parts to merge); with 16 and 32 units, head_dim 64 with one query
+  // head per KV head at batch 128 took 25.6 and 38.7 us against 23.
+  constexpr int kTeamUnits = 8;
+  const int G = max(1, SUB == 1 ? min(n_wg, U) : min(n_wg * SUB, max(min(n_wg, U), U / kTeamUnits)));
   // Rows without units: zeros for an empty decode context, NaN for a contract
-  // violation (flagged in s_tail above); rows r = bid (mod G) are this
+  // violation (flagged in s_tail above); rows r = wg (mod n_wg) are this
   // workgroup's to write.
-  for (int r = bid; r < R; r += G_) {
+  for (int r = wg; r < R; r += n_wg) {
     if (s_cum[r + 1] != s_cum[r]) continue;  // the row has units
     const int code = s_tail[r];
     if (code != kRowZeros && code != kRowNaN) continue;
@@ -332,13 +349,19 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, D
     T* o = reinterpret_cast<T*>(a.out) + (int64_t)qrow * a.H_q * D;
     for (int i = tid; i < a.H_q * D; i += NT) store_out<T>(o + i, fill);
   }
-  if (bid >= G || U == 0) return;
-  const int u0 = range_begin(bid, U, G), u1 = range_begin(bid + 1, U, G);
-  const int n_units = u1 - u0;
+  if (wg >= G || U == 0) return;
+  auto units_of = [&](int x) { return x < G ? range_begin(x + 1, U, G) - range_begin(x, U, G) : 0; };
+  const int u0 = range_begin(min(bid, G), U, G);
+  const int n_units = units_of(bid);
+  int n_steps = n_units;  // the longest range of the workgroup's teams
+  if constexpr (SUB > 1) {
+#pragma unroll
+    for (int t = 0; t < SUB; ++t) n_steps = max(n_steps, units_of(t * n_wg + wg));
+  }
 
   // 2. unit table of this range, and the items cut by its start and its end
   const BlockTable bt{a.block_table, a.bt_stride};
-  for (int i = tid; i < n_units; i += NT) {
+  for (int i = w * 64 + lane; i < n_units; i += 64 * W) {
     const int u = u0 + i;
     const int r = info_row_seq(s_cum, R, a.nb, u);
     const int np = s_cum[r + 1] - s_cum[r];
@@ -350,15 +373,13 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, D
     s_info[i] = valid | (p == 0) << 5 | (p == np - 1) << 6 | hb << 7 | qrow << 13;
     if (i == 0 || i == n_units - 1) {
       const CutItem cut{range_of(u - p, U, G), range_of(u - p + np - 1, U, G)};
-      if (i == 0) sm.cut[0] = p == 0 ? CutItem{-1, -1} : cut;
-      if (i == n_units - 1) sm.cut[1] = p == np - 1 ? CutItem{-1, -1} : cut;
+      if (i == 0) tm.cut[0] = p == 0 ? CutItem{-1, -1} : cut;
+      if (i == n_units - 1) tm.cut[1] = p == np - 1 ? CutItem{-1, -1} : cut;
     }
   }
   __syncthreads();
 
   // 3. stream the units: wave w handles KV head hb * W + w of every unit
-  const int lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int dl = lane % Sh::LPT, row = lane / Sh::LPT;
   const int lane_off = lane * 16;
   const T* kp = reinterpret_cast<const T*>(a.k_pages);
@@ -420,7 +441,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, D
   auto of_job = [](int j, int v0, int v1) { return j == 0 ? v0 : v1; };
   auto job_begin = [&](auto j_, int qrow, int g) {
     constexpr int j = decltype(j_)::value;
-    const CutItem cut = sm.cut[j];
+    const CutItem cut = tm.cut[j];
     phase[j] = 1;
     level[j] = cut.grouped() && !cut.group_of_one(bid) ? 0 : 1;
     job_row[j] = qrow;
@@ -441,12 +462,12 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, D
   auto jobs_step = [&]() {  // after a barrier
     if ((phase[0] | phase[1]) < 2) return;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) phase[j] = phase[j] == 3 ? sm.last[j] ? 4 : 0 : phase[j];
+    for (int j = 0; j < 2; ++j) phase[j] = phase[j] == 3 ? tm.last[j] ? 4 : 0 : phase[j];
     if (w == 0 && lane < 2) {
       const int ph = of_job(lane, phase[0], phase[1]), lv = of_job(lane, level[0], level[1]);
       if (ph == 2) {
-        const CutItem cut = sm.cut[lane];
-        sm.last[lane] = counter_arrive(a.ws_flag + (int64_t)cut.counter(lv, bid) * W, a.tag, cut.parts(lv, bid));
+        const CutItem cut = tm.cut[lane];
+        tm.last[lane] = counter_arrive(a.ws_flag + (int64_t)cut.counter(lv, bid) * W, a.tag, cut.parts(lv, bid));
       }
     }
 #pragma unroll
@@ -504,11 +525,11 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, D
           mfma::finish<D, S, T>(ms, lane, outp);
         else
           finish_rows<T, D, S>(st, row, dl, outp);
-      } else {  // (workgroup-uniform)
+      } else {  // (uniform over the team)
         if constexpr (MF) {
           if (held_now && k == n_units - 1) {
             merge_held<T, D, S>(ms, held_rec, lane, outp);
-            if (tid == 0) counter_reset(a.ws_flag + (int64_t)bid * W, a.tag);
+            if (w == 0 && lane == 0) counter_reset(a.ws_flag + (int64_t)bid * W, a.tag);
             return;
           }
         }
@@ -524,7 +545,9 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, D
   };
   // The jobs left when the range has streamed.
   auto jobs_finish = [&]() {
-    while (phase[0] | phase[1]) {  // workgroup-uniform
+    // (every team runs every step of a two-level merge: stored and counted,
+    // merged and stored, counted, merged)
+    for (int step = 0; SUB > 1 ? step < 4 : (phase[0] | phase[1]) != 0; ++step) {
       jobs_stored(std::integral_constant<int, 0>{});
       __syncthreads();
       jobs_step();
@@ -532,7 +555,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, D
       for (int j = 0; j < 2; ++j) {
         if (of_job(j, phase[0], phase[1]) != 4) continue;
         const int lv = of_job(j, level[0], level[1]);
-        const CutItem cut = sm.cut[j];
+        const CutItem cut = tm.cut[j];
         T* outp = reinterpret_cast<T*>(a.out) + ((int64_t)of_job(j, job_row[0], job_row[1]) * a.H_q +
                                                  (int64_t)of_job(j, job_g[0], job_g[1]) * S) * D;
         using Rec = std::conditional_t<MF, mfma::Record<D, S>, RowsRecord<D, S>>;
@@ -596,53 +619,64 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, D
     // counter again in this call), the record's latency hidden behind the
     // unit's fold.  With a single unit the counter is loaded between its K and
     // V loads and looked at before it starts.
-    const bool held = sm.cut[1].x0 == bid && sm.cut[1].x1 == bid + 1;
+    const bool held = n_units > 0 && tm.cut[1].x0 == bid && tm.cut[1].x1 == bid + 1;
     const unsigned long long counted = a.tag | 1ull;  // one part counted
     u32x2_t ctr = u32x2_t{0u, 0u};
 
-    u32x4 kc[Sh::NI], vc[Sh::NI];
-    load_queries(__builtin_amdgcn_readfirstlane(s_info[0]));
-    tile_k(0, kc);
-    if (held && w == 0 && n_units == 1) asm_load_dev(a.ws_flag + (int64_t)bid * W, ctr);
-    tile_v(0, vc);
-    auto look = [&](auto newer) {  // newer: the tile loads issued after the counter's
-      vm_wait<decltype(newer)::value>(ctr);
-      if (lane == 0) sm.held = ((unsigned long long)ctr.y << 32 | ctr.x) == counted;
-    };
-    if (held && w == 0 && n_units == 1) look(std::integral_constant<int, Sh::NI>{});
-    for (int k = 0; k < n_units; ++k) {
-      __syncthreads();  // lockstep, as in begin_unit
-      jobs_step();
-      const int info = __builtin_amdgcn_readfirstlane(s_info[k]);
-      if (info_start(info) || k == 0) {
-        head_partial = !info_start(info);
-        mfma::reset<D, S>(ms);
-      }
-      vm_wait<Sh::NI>(kc);  // K of unit k and the queries (issued before it)
-      vm_wait<Sh::NI>(ms.qt);
-      if (held && w == 0 && k + 2 == n_units) asm_load_dev(a.ws_flag + (int64_t)bid * W, ctr);
-      if (held && k == n_units - 1) {
-        held_now = sm.held;
-        if (held_now) {
-          const int64_t slot = ((int64_t)(bid + 1) * 2 + 0) * W + w;
-          load_held<D, S>(held_rec, a.ws_o + slot * S * D, a.ws_ml + slot * S * 2, lane);
+    // (one block for a team with units, left only past the last wait: no path
+    // leads from a load around its wait)
+    if (SUB == 1 || n_units > 0) {
+      u32x4 kc[Sh::NI], vc[Sh::NI];
+      load_queries(__builtin_amdgcn_readfirstlane(s_info[0]));
+      tile_k(0, kc);
+      if (held && w == 0 && n_units == 1) asm_load_dev(a.ws_flag + (int64_t)bid * W, ctr);
+      tile_v(0, vc);
+      auto look = [&](auto newer) {  // newer: the tile loads issued after the counter's
+        vm_wait<decltype(newer)::value>(ctr);
+        if (lane == 0) tm.held = ((unsigned long long)ctr.y << 32 | ctr.x) == counted;
+      };
+      if (held && w == 0 && n_units == 1) look(std::integral_constant<int, Sh::NI>{});
+      int k = 0;
+      do {
+        __syncthreads();  // lockstep, as in begin_unit
+        jobs_step();
+        const int info = __builtin_amdgcn_readfirstlane(s_info[k]);
+        if (info_start(info) || k == 0) {
+          head_partial = !info_start(info);
+          mfma::reset<D, S>(ms);
         }
-      }
-      mfma::s16x4_t phi, plo;
-      mfma::fold_qk<D, S>(ms, kc, s_kv[w], lane, info_valid(info), a.scale_log2, phi, plo);
-      if (k + 1 < n_units) {  // the queries are free once the QK half is done
-        const int next = __builtin_amdgcn_readfirstlane(s_info[k + 1]);
-        if (info_start(next)) load_queries(next);
-      }
-      tile_k(k + 1, kc);
-      jobs_stored(std::integral_constant<int, (Sh::NI & 15) | (7 << 4) | (15 << 8)>{});
-      vm_wait<Sh::NI>(vc);  // V of unit k
-      mfma::fold_pv<D, S>(ms, vc, s_kv[w], lane, phi, plo);
-      tile_v(k + 1, vc);
-      end_unit(k, info);
-      if (held && w == 0 && k + 2 == n_units) look(std::integral_constant<int, 2 * Sh::NI>{});
+        vm_wait<Sh::NI>(kc);  // K of unit k and the queries (issued before it)
+        vm_wait<Sh::NI>(ms.qt);
+        if (held && w == 0 && k + 2 == n_units) asm_load_dev(a.ws_flag + (int64_t)bid * W, ctr);
+        if (held && k == n_units - 1) {
+          held_now = tm.held;
+          if (held_now) {
+            const int64_t slot = ((int64_t)(bid + 1) * 2 + 0) * W + w;
+            load_held<D, S>(held_rec, a.ws_o + slot * S * D, a.ws_ml + slot * S * 2, lane);
+          }
+        }
+        mfma::s16x4_t phi, plo;
+        mfma::fold_qk<D, S>(ms, kc, s_kv[wave], lane, info_valid(info), a.scale_log2, phi, plo);
+        if (k + 1 < n_units) {  // the queries are free once the QK half is done
+          const int next = __builtin_amdgcn_readfirstlane(s_info[k + 1]);
+          if (info_start(next)) load_queries(next);
+        }
+        tile_k(k + 1, kc);
+        jobs_stored(std::integral_constant<int, (Sh::NI & 15) | (7 << 4) | (15 << 8)>{});
+        vm_wait<Sh::NI>(vc);  // V of unit k
+        mfma::fold_pv<D, S>(ms, vc, s_kv[wave], lane, phi, plo);
+        tile_v(k + 1, vc);
+        end_unit(k, info);
+        if (held && w == 0 && k + 2 == n_units) look(std::integral_constant<int, 2 * Sh::NI>{});
+      } while (++k < n_units);
+      vm_wait<0>(kc);  // the last (null) tiles' loads, before their registers serve anything else
+      vm_wait<0>(vc);
     }
-    __builtin_amdgcn_s_waitcnt(0);  // the last (null) tiles' loads
+    for (int k = n_units; k < n_steps; ++k) {  // another team has a unit more
+      __syncthreads();
+      jobs_step();
+      jobs_stored(std::integral_constant<int, 0>{});
+    }
     jobs_finish();
   } else {
     // A ring of NBUF register tiles: the tile of unit k + NBUF - 1 is issued
@@ -653,7 +687,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, D
     u32x4 kr[NBUF][Sh::NI], vr[NBUF][Sh::NI];
 #pragma unroll
     for (int u = 0; u + 1 < NBUF; ++u) issue(kr[u], vr[u], u);
-    for (int base = 0; base < n_units; base += NBUF) {
+    for (int base = 0; base < n_steps; base += NBUF) {
 #pragma unroll
       for (int u = 0; u < NBUF; ++u) {
         const int k = base + u;
@@ -662,7 +696,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, D
         jobs_stored(std::integral_constant<int, kWaitRing>{});
         if (k < n_units) {
           if constexpr (MF)
-            mfma::fold<D, S>(ms, kr[u], vr[u], s_kv[w], lane, info_valid(info), a.scale_log2);
+            mfma::fold<D, S>(ms, kr[u], vr[u], s_kv[wave], lane, info_valid(info), a.scale_log2);
           else
             fold_tile<T, D, S>(st, kr[u], vr[u], row, info_valid(info), a.scale_log2);
           end_unit(k, info);

@@ -4,8 +4,8 @@
 
 namespace pa {
 
-template const void* stream_pick<uint16_t, 64, false>(int, int);
-template const void* stream_pick<float, 128, false>(int, int);
-template const void* stream_pick<float, 64, false>(int, int);
+template const void* stream_pick<uint16_t, 64, false>(int, int, int);
+template const void* stream_pick<float, 128, false>(int, int, int);
+template const void* stream_pick<float, 64, false>(int, int, int);
 
 }  // namespace pa

@@ -6,7 +6,7 @@
 
 namespace pa {
 
-template const void* stream_pick<uint16_t, 128, true>(int, int);
+template const void* stream_pick<uint16_t, 128, true>(int, int, int);
 
 __global__ __launch_bounds__(256) void fill_i64_kernel(int64_t* p, int64_t n, int64_t value) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = value;

@@ -4,8 +4,8 @@
 
 namespace pa {
 
-template const void* stream_pick<uint16_t, 64, true>(int, int);
-template const void* stream_pick<float, 128, true>(int, int);
-template const void* stream_pick<float, 64, true>(int, int);
+template const void* stream_pick<uint16_t, 64, true>(int, int, int);
+template const void* stream_pick<float, 128, true>(int, int, int);
+template const void* stream_pick<float, 64, true>(int, int, int);
 
 }  // namespace pa

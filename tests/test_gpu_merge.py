@@ -94,3 +94,29 @@ def test_recorded_launch_replays():
             call()
             torch.cuda.synchronize()
             assert torch.equal(out, ref), f"eager after replay {i}"
+
+
+@pytest.mark.parametrize("H_kv,dtype,D", [(1, "bf16", 128), (2, "bf16", 64), (4, "fp32", 128), (3, "bf16", 128)])
+@pytest.mark.parametrize("pages", [None, 1000])
+def test_teams_of_fewer_heads(H_kv, dtype, D, pages):
+    """Fewer than 8 KV heads: several ranges per workgroup, which end at
+    different units (contexts of 0 to 40 pages, some teams without a range);
+    with a declared bound of 1,000 pages for each of 600 sequences, past the
+    teams' unit tables, one range per workgroup."""
+    announce(f"teams H_kv={H_kv} {dtype} D={D} bound={pages}")
+    rng = np.random.default_rng(H_kv)
+    ctx = [int(x) for x in rng.integers(0, 640, size=600 if pages else 37)]
+    b = W.generate("tiny", seed=H_kv, dtype=dtype, overrides=dict(H_q=4 * H_kv, H_kv=H_kv, D=D, ctx=("list", ctx),
+                                                                  pool=("factor", 1.2)))
+    ref = run_oracle(b)
+    if pages:
+        table = np.zeros((b.num_seqs, pages), np.int32)
+        table[:, :b.block_table.shape[1]] = b.block_table
+        b = W.Batch(**{**b.__dict__, "block_table": table})
+    dev = upload(b)
+    out = torch.full_like(dev["q"], float("nan"))
+    dims = pb.make_dims(dev["q"], dev["k"], dev["bt"], 16 * pages if pages else int(b.context_lens.max()))
+    for _ in range(3):
+        pb.paged_attn(dev["q"], dev["k"], dev["v"], dev["bt"], dev["cl"], b.scale, out, dims)
+    torch.cuda.synchronize()
+    assert_parity(out.float().cpu().numpy(), ref, strict=False, what="teams")
