@@ -370,9 +370,10 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
       const int g_dec = G < cus - g_pf ? G : (cus - g_pf > p.g_min ? cus - g_pf : (int)p.g_min);
       e = pa::launch_mixed(p.s, sa, pf, g_dec, g_dec + g_pf, stream, next_events());
     } else {
-      const int per_cu = pa::prefill_occupancy(dims->head_dim, p.s, dims->num_seqs);
+      const int blocks = pa::prefill_blocks(p.s, dims->num_kv_heads, dims->num_q_rows, dims->num_seqs, cus);
+      const int per_cu = pa::prefill_occupancy(dims->head_dim, p.s, blocks, dims->num_seqs);
       if (per_cu <= 0) return PA_EHIP;
-      e = pa::launch_prefill(dims->head_dim, p.s, pf, per_cu * cus, stream, next_events());
+      e = pa::launch_prefill(dims->head_dim, p.s, blocks, pf, per_cu * cus, stream, next_events());
     }
     if (e != hipSuccess) return PA_EHIP;
   }

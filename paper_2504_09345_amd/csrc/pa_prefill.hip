@@ -11,7 +11,8 @@
 // Work item: (sequence, KV head g, block of PB chunk positions).  The block's
 // M = PB * s query rows (position-major, the s heads of group g) are split
 // over 8 waves of two 16-row MFMA blocks each (256 rows), so every operand
-// read from LDS feeds two matrix products.  Per step of two 16-key pages:
+// read from LDS feeds two matrix products (or of one block each, 128 rows, in
+// calls too small to fill the CUs: prefill_blocks).  Per step of two 16-key pages:
 //   S^T[key][row] = K . Q^T   (v_mfma_f32_16x16x32_bf16 per page, K as the A
 //                  operand)
 //   online softmax per row (each lane owns one row and 8 of its keys)
@@ -54,36 +55,56 @@
 
 namespace pa {
 
-template <int D, int S, bool TR>
+template <int D, int S, bool TR, int NB>
 __global__ __launch_bounds__(kPfThreads) void prefill_kernel(PrefillArgs a) {
   __shared__ PrefillSmem sm;
   extern __shared__ int32_t s_cum[];  // [B + 1] prefix of items per sequence
-  prefill_body<D, S, TR>(a, sm, s_cum, blockIdx.x, gridDim.x);
+  prefill_body<D, S, TR, NB>(a, sm, s_cum, blockIdx.x, gridDim.x);
 }
 
-template <int D, bool TR>
+template <int D, bool TR, int NB>
 static const void* prefill_pick(int s) {
   switch (s) {
-    case 1: return reinterpret_cast<const void*>(&prefill_kernel<D, 1, TR>);
-    case 2: return reinterpret_cast<const void*>(&prefill_kernel<D, 2, TR>);
-    case 4: return reinterpret_cast<const void*>(&prefill_kernel<D, 4, TR>);
-    case 6: return reinterpret_cast<const void*>(&prefill_kernel<D, 6, TR>);
-    case 8: return reinterpret_cast<const void*>(&prefill_kernel<D, 8, TR>);
+    case 1: return reinterpret_cast<const void*>(&prefill_kernel<D, 1, TR, NB>);
+    case 2: return reinterpret_cast<const void*>(&prefill_kernel<D, 2, TR, NB>);
+    case 4: return reinterpret_cast<const void*>(&prefill_kernel<D, 4, TR, NB>);
+    case 6: return reinterpret_cast<const void*>(&prefill_kernel<D, 6, TR, NB>);
+    case 8: return reinterpret_cast<const void*>(&prefill_kernel<D, 8, TR, NB>);
   }
   return nullptr;
 }
 
 // trace: the gather-trace instantiation (also records the rows it loads)
-static const void* prefill_fn(int D, int s, bool trace = false) {
-  if (D == 128) return trace ? prefill_pick<128, true>(s) : prefill_pick<128, false>(s);
-  if (D == 64) return trace ? prefill_pick<64, true>(s) : prefill_pick<64, false>(s);
+template <int NB>
+static const void* prefill_fn_blocks(int D, int s, bool trace) {
+  if (D == 128) return trace ? prefill_pick<128, true, NB>(s) : prefill_pick<128, false, NB>(s);
+  if (D == 64) return trace ? prefill_pick<64, true, NB>(s) : prefill_pick<64, false, NB>(s);
   return nullptr;
 }
+static const void* prefill_fn(int D, int s, int blocks, bool trace = false) {
+  return blocks == 1 ? prefill_fn_blocks<1>(D, s, trace) : prefill_fn_blocks<kPfBlocksMax>(D, s, trace);
+}
 
-bool prefill_supported(int dtype, int D, int s) { return dtype == 0 && prefill_fn(D, s) != nullptr; }
+bool prefill_supported(int dtype, int D, int s) { return dtype == 0 && prefill_fn(D, s, kPfBlocksMax) != nullptr; }
 
-int prefill_occupancy(int D, int s, int B) {
-  const void* fn = prefill_fn(D, s);
+// With no more items of 128 rows than CUs, all run at once and the longest
+// item's chain of steps is the call's time: a step with one block per wave has
+// half the products and half the softmax's vector work, at the same staging.
+// 32 query heads over 8: one chunk of 700 rows 31.1 us with 256-row items and
+// 22.5 with 128, 1,000 rows 38.5 and 28.8, 8 of 60-100 rows on 0-1,000 tokens
+// 39.8 and 29.3; one KV head of 8 query heads, 2,048 rows on 1,000 tokens 97.6
+// and 70.4.  Past the line items wait for a second round, or share a CU: one
+// chunk of 1,030 rows 40.5 and 47.5, 1,500 rows 52.7 and 73.3, 2,000 rows on
+// 2,000 tokens 127 and 146, 20 of 60-90 rows on 0-2,000 tokens 69.7 and 87.0.
+// The host knows no lengths: `seqs` chunks of `rows` positions in all have at
+// most this many blocks.
+int prefill_blocks(int s, int H_kv, int rows, int seqs, int cus) {
+  const int pb = pf_rows(1) / s;  // positions per item
+  return ((int64_t)rows + (int64_t)(pb - 1) * seqs) / pb * H_kv <= cus ? 1 : kPfBlocksMax;
+}
+
+int prefill_occupancy(int D, int s, int blocks, int B) {
+  const void* fn = prefill_fn(D, s, blocks);
   if (fn == nullptr) return 0;
   int n = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, kPfThreads, (size_t)(B + 1) * sizeof(int32_t)) != hipSuccess)
@@ -91,8 +112,8 @@ int prefill_occupancy(int D, int s, int B) {
   return n;
 }
 
-hipError_t launch_prefill(int D, int s, const PrefillArgs& a, int G, hipStream_t st, KernelEvents ev) {
-  const void* fn = prefill_fn(D, s, a.trace != nullptr);
+hipError_t launch_prefill(int D, int s, int blocks, const PrefillArgs& a, int G, hipStream_t st, KernelEvents ev) {
+  const void* fn = prefill_fn(D, s, blocks, a.trace != nullptr);
   if (fn == nullptr || G <= 0) return hipErrorInvalidValue;
   void* args[] = {const_cast<PrefillArgs*>(&a)};
   hipError_t e = hipExtLaunchKernel(fn, dim3(G), dim3(kPfThreads), args, (size_t)(a.B + 1) * sizeof(int32_t), st,

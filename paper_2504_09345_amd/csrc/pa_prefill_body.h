@@ -20,8 +20,10 @@ template <bool V> struct PfBool { static constexpr bool value = V; };
 
 constexpr int kPfWaves = 8;
 constexpr int kPfThreads = 64 * kPfWaves;
-constexpr int kPfBlocks = 2;                       // 16-row MFMA blocks per wave
-constexpr int kPfRows = 16 * kPfBlocks * kPfWaves;  // 256 query rows per item
+// 16-row MFMA blocks per wave, and query rows per item: 256, or 128 for a call
+// that would leave CUs idle with 256 (prefill_blocks)
+constexpr int kPfBlocksMax = 2;
+constexpr int pf_rows(int blocks) { return 16 * blocks * kPfWaves; }
 constexpr int kPfMaxPages = 2048;                  // block-table window in LDS (power of 2)
 constexpr int kPfStepBytes = 8192;                 // K (and V) bytes of a synchronised step
 template <int D> constexpr int kPfStep = kPfStepBytes / (kPage * D * 2);  // its pages: 2 at D = 128, 4 at 64
@@ -42,16 +44,17 @@ struct PrefillSmem {
 };
 
 // Prefill workgroup `bid` of a grid of G; s_cum holds B + 1 ints of LDS.
+// kPfBlocks: 16-row blocks per wave.
 // TR: gather-trace instantiation (records every loaded token's pool row in
 // a.trace besides computing the attention).
-template <int D, int S, bool TR = false>
+template <int D, int S, bool TR = false, int kPfBlocks = kPfBlocksMax>
 __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& sm, int32_t* s_cum, int bid,
                                              int G) {
   // V and P in fp16 (one product) with a bf16 pass where that does not hold, or
   // only the bf16 pass
   constexpr bool kF16 = D == 128;
   constexpr int kPfStep = pa::kPfStep<D>;
-  constexpr int PB = kPfRows / S;       // chunk positions per item
+  constexpr int PB = pf_rows(kPfBlocks) / S;      // chunk positions per item
   constexpr int KSTEPS = D / 32;        // QK MFMA steps over dims
   constexpr int MB = D / 16;            // PV MFMA blocks over dims
   constexpr int KT = kPage * D * 2;     // bytes of one tile
@@ -133,7 +136,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
     // block-table window: s_bt[p % kPfMaxPages] holds the entry of page p
     for (int i = tid; i < min(npg, kPfMaxPages); i += kPfThreads) s_bt[i] = bt.page(b, i);
 
-    // this lane's rows: block rb, row m = (w * 2 + rb) * 16 + lane % 16
+    // this lane's rows: block rb, row m = (w * kPfBlocks + rb) * 16 + lane % 16
     u32x4 qt[kPfBlocks][KSTEPS];
     int lim[kPfBlocks];
     float mrow[kPfBlocks];
@@ -198,7 +201,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
       }
     };
     // S^T = K . Q^T for the pages of step t (A: key lane%16, dims 32 st +
-    // 8 (lane/16) .. +8), each K read shared by both row blocks
+    // 8 (lane/16) .. +8), each K read shared by the row blocks
     // (the step's K operands are read from LDS first, all at once, so their
     // latency overlaps the staging work issued before the products)
     typedef u32x4 KOps[kPfStep][KSTEPS];
@@ -497,7 +500,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
     }
 
     // normalise and store straight from the accumulators: lane (n, Gq) holds
-    // dims 16 mb + 4 Gq + i of row (w * 2 + rb) * 16 + n
+    // dims 16 mb + 4 Gq + i of row (w * kPfBlocks + rb) * 16 + n
 #pragma unroll
     for (int rb = 0; rb < kPfBlocks; ++rb) {
       if (lim[rb] >= 0) {
