@@ -26,10 +26,11 @@
  * Conventions for every entry point
  *   - All array pointers are DEVICE pointers (HBM), except where a name ends
  *     in _host.  The caller owns every buffer; the library allocates nothing.
- *     Its only state between calls is a process-wide tag of the workspaces'
- *     arrival counters (it never changes a result).  Calls on
- *     different streams may overlap as long as their output and workspace
- *     buffers do not.
+ *     Its only state between calls is the number of calls made (which keys the
+ *     workspaces' arrival counters and never changes a result).  A workspace
+ *     may hold anything when a call begins, and the caller may use it for
+ *     anything between calls.  Calls on different streams may overlap as long
+ *     as their output and workspace buffers do not.
  *   - Work is enqueued on `stream` (NULL = the null stream) and the call
  *     returns without synchronising.  Faults inside kernels (for example a
  *     block-table entry outside the pool) surface at the caller's next
@@ -179,9 +180,12 @@ int paged_attn_varlen(const void *q, const void *k_pages, const void *v_pages,
  *     fp32 and head_dim 64 chunk rows
  *     need rows x H_q x splits x (D + 2) x 4 bytes.
  *   - Every call on one GPU shares that GPU's array and leaves its contents
- *     behind (a counter is left ready for the next call, and anything else in
- *     its place is recognised, so nothing needs clearing): calls that overlap in time on one GPU (other streams,
- *     other threads) race on it and must be serialised by the caller.
+ *     behind (counters are keyed by call, so nothing needs clearing): calls
+ *     that overlap in time on one GPU (other streams, other threads) race on
+ *     it and must be serialised by the caller.  Such a race spoils the calls
+ *     in it; where one of them is a replay of a recorded call (which keeps its
+ *     key), also that recording's later replays, until a call of another key
+ *     has used the same counters.
  *   - Decode-only callers pass query_start_loc = {0, 1, ..., num_seqs} with
  *     num_q_rows = num_seqs and max_q_len = 1, which runs exactly the kernels
  *     of paged_attn.

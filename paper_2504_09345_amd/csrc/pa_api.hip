@@ -1,7 +1,8 @@
 // C ABI of libpagedattn.so: host-side validation, launch planning and
 // dispatch.  Validation runs before any HIP call, so a rejected call enqueues
 // nothing and is testable without a GPU.  The library allocates nothing; its
-// only state between calls is the tag of the workspaces' arrival counters.
+// only state between calls is the number of calls made, which keys the
+// workspaces' arrival counters.
 #include <climits>
 #include <math.h>
 #include <stddef.h>
@@ -11,6 +12,7 @@
 #include <chrono>
 #include <mutex>
 
+#include "pa_counter.h"
 #include "pa_kernels.h"
 #include "pa_sched.h"
 #include "pagedattn.h"
@@ -140,19 +142,13 @@ int plan(const pa_dims_t* d, bool varlen, Plan* p) {
   return PA_OK;
 }
 
-// Tag of the arrival counters in workspaces: 48 bits drawn once per process (a
-// mixed clock reading, never 0), so that what a fresh workspace holds does not
-// look like a counter.  It does not influence any result.
-unsigned long long counter_tag() {
-  static const unsigned long long tag = [] {
-    unsigned long long x = (unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count() ^
-                           (unsigned long long)std::chrono::system_clock::now().time_since_epoch().count() << 20;
-    x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
-    x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
-    x = (x ^ (x >> 31)) & ~0xffffull;
-    return x != 0 ? x : 0x9e3779b97f4a0000ull;
-  }();
-  return tag;
+// A number that no other call of the process has, from a clock reading on (so
+// that neither do another process's calls, whose memory a workspace may have
+// been): it makes the call's counter key and influences no result.
+uint64_t next_call() {
+  static std::atomic<uint64_t> n{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() ^
+                                 (uint64_t)std::chrono::system_clock::now().time_since_epoch().count() << 20};
+  return n.fetch_add(1, std::memory_order_relaxed);
 }
 
 // Fixed device scratch of paged_attn_varlen_noalloc: the workspace of a call
@@ -297,7 +293,7 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
     sa.ws_o = reinterpret_cast<float*>(ws);
     sa.ws_ml = reinterpret_cast<float*>(ws + p.st_o);
     sa.ws_flag = reinterpret_cast<unsigned long long*>(ws + p.st_o + p.st_ml);
-    sa.tag = counter_tag();
+    sa.key = pa::counter_key(next_call());
     sa.bt_stride = dims->max_pages_per_seq;
     sa.scale_log2 = scale * 1.4426950408889634f;
     sa.B = dims->num_seqs;

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "pa_counter.h"
+
 namespace pa {
 
 // Arguments of the split-K attention kernel.  Flat grid of
@@ -62,7 +64,7 @@ struct StreamArgs {
   float* ws_o;       // [G][2][W][s][D] partial outputs (slot 0 head, 1 tail)
   float* ws_ml;      // [G][2][W][s][2]
   unsigned long long* ws_flag;  // [G][W] arrival counters of cut items (the first of each range's W)
-  unsigned long long tag;       // upper 48 bits of the counters (the process's; lower 16 bits 0)
+  CounterKey key;               // this call's step of the counters
   int64_t bt_stride;
   float scale_log2;
   int B, H_q, H_kv, max_context_len;

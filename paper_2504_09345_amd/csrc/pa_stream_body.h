@@ -5,6 +5,7 @@
 
 #include <type_traits>
 
+#include "pa_counter.h"
 #include "pa_device.h"
 #include "pa_kernels.h"
 #include "pa_tile.h"
@@ -171,39 +172,27 @@ __device__ __forceinline__ void merge_held(const mfma::State<D, S>& st, const He
   }
 }
 
-// Arrival counters of cut items, one per range, counted once per workgroup.  A
-// counter's upper 48 bits carry the process's tag, its lower 16 bits the parts
-// counted; between calls it holds the tag and 0, left so by the part that
-// completed it, and a part counts with one fetch-and-add.  Anything else is
-// found only the first time a workspace (or that place of it) is used: the
-// parts that meet it put the tag in its place and count again, so nothing
-// needs clearing beforehand.  Device-scope atomics on one line complete about
-// 30 ns apart, so they are kept few: with every wave counting by itself, in a
-// compare-and-swap loop that retries once per other part, 8 sequences cut into
-// 26 parts each took 60 us.
-__device__ __forceinline__ bool counter_tagged(unsigned long long v, unsigned long long tag) {
-  return (v & ~0xffffull) == tag;
-}
-__device__ __forceinline__ void counter_reset(unsigned long long* ctr, unsigned long long tag) {
-  __hip_atomic_store(ctr, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// Count one part and tell whether it completes the counter's n.
-__device__ __forceinline__ bool counter_arrive(unsigned long long* ctr, unsigned long long tag, int n) {
-  unsigned long long old = __hip_atomic_fetch_add(ctr, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  while (!counter_tagged(old, tag)) {
-    // (a failed swap met another part's; each changes the counter a bounded
-    // number of times, and once tagged it stays so)
-    unsigned long long now = old + 1;
-    while (!counter_tagged(now, tag) &&
-           !__hip_atomic_compare_exchange_strong(ctr, &now, tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT)) {
-    }
-    old = __hip_atomic_fetch_add(ctr, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Arrival counters of cut items (pa_counter.h), one per range, counted once per
+// workgroup.  Device-scope atomics on one line complete about 30 ns apart, so
+// they are kept few, one fetch-and-add per part: with every wave counting by
+// itself, in a compare-and-swap loop that retries once per other part, 8
+// sequences cut into 26 parts each took 60 us.
+struct DeviceCounter {
+  unsigned long long* p;
+  __device__ __forceinline__ uint64_t fetch_add(uint64_t x) {
+    return __hip_atomic_fetch_add(p, (unsigned long long)x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  const bool last = (int)(old & 0xffffull) == n - 1;
-  if (last) counter_reset(ctr, tag);
-  return last;
-}
+  __device__ __forceinline__ bool swap(uint64_t& expected, uint64_t x) {
+    unsigned long long e = expected;
+    const bool done = __hip_atomic_compare_exchange_strong(p, &e, (unsigned long long)x, __ATOMIC_RELAXED,
+                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    expected = e;
+    return done;
+  }
+  __device__ __forceinline__ void store(uint64_t x) {
+    __hip_atomic_store(p, (unsigned long long)x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+};
 
 // An item cut over ranges x0 .. x1 merges its n = x1 - x0 + 1 records at once
 // when n <= 16, and otherwise in two levels: the last part of each group of
@@ -467,7 +456,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
       const int ph = of_job(lane, phase[0], phase[1]), lv = of_job(lane, level[0], level[1]);
       if (ph == 2) {
         const CutItem cut = tm.cut[lane];
-        tm.last[lane] = counter_arrive(a.ws_flag + (int64_t)cut.counter(lv, bid) * W, a.tag, cut.parts(lv, bid));
+        DeviceCounter ctr{a.ws_flag + (int64_t)cut.counter(lv, bid) * W};
+        tm.last[lane] = counter_arrive(ctr, a.key, cut.parts(lv, bid));
       }
     }
 #pragma unroll
@@ -529,7 +519,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
         if constexpr (MF) {
           if (held_now && k == n_units - 1) {
             merge_held<T, D, S>(ms, held_rec, lane, outp);
-            if (w == 0 && lane == 0) counter_reset(a.ws_flag + (int64_t)bid * W, a.tag);
+            if (w == 0 && lane == 0) DeviceCounter{a.ws_flag + (int64_t)bid * W}.store(0);
             return;
           }
         }
@@ -620,7 +610,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
     // unit's fold.  With a single unit the counter is loaded between its K and
     // V loads and looked at before it starts.
     const bool held = n_units > 0 && tm.cut[1].x0 == bid && tm.cut[1].x1 == bid + 1;
-    const unsigned long long counted = a.tag | 1ull;  // one part counted
+    const uint64_t counted = a.key.step;  // one part counted
     u32x2_t ctr = u32x2_t{0u, 0u};
 
     // (one block for a team with units, left only past the last wait: no path
@@ -633,7 +623,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
       tile_v(0, vc);
       auto look = [&](auto newer) {  // newer: the tile loads issued after the counter's
         vm_wait<decltype(newer)::value>(ctr);
-        if (lane == 0) tm.held = ((unsigned long long)ctr.y << 32 | ctr.x) == counted;
+        if (lane == 0) tm.held = ((uint64_t)ctr.y << 32 | ctr.x) == counted;
       };
       if (held && w == 0 && n_units == 1) look(std::integral_constant<int, Sh::NI>{});
       int k = 0;

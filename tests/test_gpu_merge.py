@@ -96,6 +96,24 @@ def test_recorded_launch_replays():
             assert torch.equal(out, ref), f"eager after replay {i}"
 
 
+@pytest.mark.parametrize("pages,low", [(13, 0x3F80), (13, 5), (2, 1), (64, 0x3F80), (64, 7), (208, 5)])
+def test_workspace_partly_written_over(pages, low):
+    """The low two bytes of every 8-byte word of the workspace written over
+    between calls (a bf16 column, small counts): the same bits each time."""
+    announce(f"merge after low bytes {low:#x} pages={pages}")
+    b = W.generate("tiny", seed=pages, overrides=dict(H_q=32, H_kv=8, D=128, ctx=("list", [16 * pages - 3]),
+                                                      pool=("factor", 1.2)))
+    dev = upload(b)
+    n = pb.pa_workspace_size(pb.make_dims(dev["q"], dev["k"], dev["bt"], 16 * pages))
+    ws = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    got = _run(b, dev, ws)
+    assert_parity(got, run_oracle(b), strict=False, what=f"{pages} parts")
+    for _ in range(3):
+        ws.view(torch.int16)[::4] = low
+        for _ in range(2):
+            assert np.array_equal(got.view(np.uint32), _run(b, dev, ws).view(np.uint32))
+
+
 @pytest.mark.parametrize("H_kv,dtype,D", [(1, "bf16", 128), (2, "bf16", 64), (4, "fp32", 128), (3, "bf16", 128)])
 @pytest.mark.parametrize("pages", [None, 1000])
 def test_teams_of_fewer_heads(H_kv, dtype, D, pages):
