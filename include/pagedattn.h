@@ -153,8 +153,9 @@ int paged_attn(const void *q, const void *k_pages, const void *v_pages,
  * fp16 (exact for bf16 magnitudes in [2^-17, 2^16)); a chunk block whose V
  * leaves that range (or holds inf / NaN), or whose output rows have an RMS
  * below 2^-14, is computed again with fp32-level P.V (P as bf16 high and low
- * parts), the form that head_dim 64 always takes.  When every sequence
- * has max_q_len > 1 rows, only the chunk kernel runs.
+ * parts).  At head_dim 64 it forms P.V with P in three bf16 parts, which carry
+ * all of an fp32 weight's bits.  When every sequence has max_q_len > 1 rows,
+ * only the chunk kernel runs.
  * Same as paged_attn, with q/out of [num_q_rows][H_q][D] and the device array
  * query_start_loc (see layouts).  Row j of a chunk of length L in a sequence
  * of context C attends to positions 0 .. C - L + j.  dims->num_q_rows must

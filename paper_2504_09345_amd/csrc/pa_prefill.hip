@@ -28,15 +28,16 @@
 // loaded, P as its bf16 high and low parts in two v_mfma_f32_16x16x32_bf16
 // (fp32-level accuracy).  Both conditions are read off the first pass's
 // output rows.
-// head_dim 64 takes the bf16 form only (its chunks ran with fp32 weights on the
-// split-K kernel before, and fp16 P would lose precision against that), four
-// pages per step, so that a step stages the same bytes and keeps as many
-// products between barriers; an item with a row that is not finite is computed
-// again row by row, so that a V that is infinite or NaN reaches only the rows
-// that see its key.  Bound by the matrix products and the softmax's vector
-// instructions like head_dim 128: 4 chunks of 200-400 rows on 0-1024 tokens
-// 177 -> 46 us (145 TFLOP/s), 8 of 512 rows 909 -> 107 us (351 TFLOP/s), 8 of
-// 2,048 rows 10.6 ms -> 0.48 ms (535 TFLOP/s).
+// head_dim 64 takes the bf16 form only, with P in three parts (its chunks ran
+// with fp32 weights on the split-K kernel before, and fp16 P or two parts would
+// hold fewer bits), four pages per step, so that a step stages the same bytes
+// and keeps as many products between barriers; an item with a row that is not
+// finite is computed again row by row, so that a V that is infinite or NaN
+// reaches only the rows that see its key.  Bound by the matrix products and the
+// softmax's vector instructions like head_dim 128: 4 chunks of 200-400 rows on
+// 0-1,024 tokens 205 -> 58 us (130 TFLOP/s), 8 of 512 rows on 768 813 -> 86 us
+// (399 TFLOP/s), 8 of 2,048 rows on 890 10.7 ms -> 0.59 ms (433 TFLOP/s); with
+// P in two parts 49, 74 and 493 us.
 // Computing the transposed products keeps "lane l % 16 = query row" in every
 // accumulator, so the softmax statistics, the P operand and the O rescale all
 // stay in the lane that owns the row: no register transposes.

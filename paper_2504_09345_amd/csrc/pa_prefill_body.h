@@ -227,9 +227,10 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
             sc[rb][pp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                 __builtin_bit_cast(bf16x8_t, kv[pp][st]), __builtin_bit_cast(bf16x8_t, qt[rb][st]), sc[rb][pp], 0, 0, 0);
     };
-    // online softmax of step t's scores and O^T += V^T . P^T.  Row sums come
-    // from the matrix cores too: acc_l += ones . P^T (every entry of a lane's
-    // acc_l holds its row's sum).
+    // online softmax of step t's scores and O^T += V^T . P^T.  With P in two
+    // parts or fp16, row sums come from the matrix cores too: acc_l += ones . P^T
+    // (every entry of a lane's acc_l holds its row's sum); with P in three they
+    // are fp32 sums of the weights, which is no slower there.
     const bf16x8_t ones = __builtin_bit_cast(
         bf16x8_t, u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
     const f16x8_t ones_h = __builtin_bit_cast(
@@ -322,23 +323,31 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
             acc[rb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va, ph[rb], acc[rb][mb], 0, 0, 0);
         }
       } else {
-        // bf16 V and P's bf16 high and low parts: two products per pair of pages
+        // bf16 V and P's bf16 parts: a product per part and pair of pages
+        constexpr int NP = mfma::kParts<D>;
 #pragma unroll
         for (int pr = 0; pr < kPfStep; pr += 2) {
-          bf16x8_t phi[kPfBlocks], plo[kPfBlocks];
+          bf16x8_t pt[kPfBlocks][NP];
 #pragma unroll
           for (int rb = 0; rb < kPfBlocks; ++rb) {
-            s16x4_t h[2], l[2];
+            mfma::Weights<NP> w[2];
 #pragma unroll
             for (int pp = 0; pp < 2; ++pp) {
               const float* w4 = pw[rb] + (pr + pp) * 4;
               const float q4[4] = {w4[0], w4[1], w4[2], w4[3]};
-              mfma::split_hi_lo(q4, h[pp], l[pp]);
+              mfma::split_parts(q4, w[pp]);
             }
-            phi[rb] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7));
-            plo[rb] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(l[0], l[1], 0, 1, 2, 3, 4, 5, 6, 7));
-            acc_l[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, phi[rb], acc_l[rb], 0, 0, 0);
-            acc_l[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, plo[rb], acc_l[rb], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+              pt[rb][i] = __builtin_bit_cast(
+                  bf16x8_t, __builtin_shufflevector(w[0].part[i], w[1].part[i], 0, 1, 2, 3, 4, 5, 6, 7));
+              if constexpr (kF16)
+                acc_l[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pt[rb][i], acc_l[rb], 0, 0, 0);
+            }
+            if constexpr (!kF16) {  // (each lane its own keys' sum; the lanes of a row add theirs at the end)
+              const float* x = pw[rb] + pr * 4;
+              acc_l[rb][0] += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+            }
           }
 #pragma unroll
           for (int mb = 0; mb < MB; ++mb) {
@@ -348,10 +357,10 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
             const s16x4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(vt + KT + off));
             const bf16x8_t va = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-            for (int rb = 0; rb < kPfBlocks; ++rb) {
-              acc[rb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, phi[rb], acc[rb][mb], 0, 0, 0);
-              acc[rb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, plo[rb], acc[rb][mb], 0, 0, 0);
-            }
+            for (int rb = 0; rb < kPfBlocks; ++rb)
+#pragma unroll
+              for (int i = 0; i < NP; ++i)
+                acc[rb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pt[rb][i], acc[rb][mb], 0, 0, 0);
           }
         }
       }
@@ -453,6 +462,8 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
       }
     } else {
       pipeline(PfBool<false>{});
+#pragma unroll
+      for (int rb = 0; rb < kPfBlocks; ++rb) acc_l[rb][0] = rows4_sum(acc_l[rb][0]);
       // A key that a row does not see has weight 0, and where its V is infinite
       // or NaN the product makes the row NaN: an item with a row that is not
       // finite is computed again row by row, each over its own keys only (the
@@ -510,8 +521,12 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
         uint16_t* orow = og + ((int64_t)(q0 + pos0 + p) * a.H_q + (int64_t)g * S + h) * D;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-          const uint32_t w0 = (uint32_t)f32_to_bf16(acc[rb][mb][0] * inv) | (uint32_t)f32_to_bf16(acc[rb][mb][1] * inv) << 16;
-          const uint32_t w1 = (uint32_t)f32_to_bf16(acc[rb][mb][2] * inv) | (uint32_t)f32_to_bf16(acc[rb][mb][3] * inv) << 16;
+          // (head_dim 64 divides, as the split-K kernel does)
+          f32x4_t o;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[i] = kF16 ? acc[rb][mb][i] * inv : acc[rb][mb][i] / acc_l[rb][0];
+          const uint32_t w0 = (uint32_t)f32_to_bf16(o[0]) | (uint32_t)f32_to_bf16(o[1]) << 16;
+          const uint32_t w1 = (uint32_t)f32_to_bf16(o[2]) | (uint32_t)f32_to_bf16(o[3]) << 16;
           *reinterpret_cast<u32x2_t*>(orow + mb * 16 + 4 * Gq) = u32x2_t{w0, w1};
         }
       }

@@ -645,8 +645,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
             load_held<D, S>(held_rec, a.ws_o + slot * S * D, a.ws_ml + slot * S * 2, lane);
           }
         }
-        mfma::s16x4_t phi, plo;
-        mfma::fold_qk<D, S>(ms, kc, s_kv[wave], lane, info_valid(info), a.scale_log2, phi, plo);
+        mfma::Weights<mfma::kParts<D>> pt;
+        mfma::fold_qk<D, S>(ms, kc, s_kv[wave], lane, info_valid(info), a.scale_log2, pt);
         if (k + 1 < n_units) {  // the queries are free once the QK half is done
           const int next = __builtin_amdgcn_readfirstlane(s_info[k + 1]);
           if (info_start(next)) load_queries(next);
@@ -654,7 +654,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
         tile_k(k + 1, kc);
         jobs_stored(std::integral_constant<int, (Sh::NI & 15) | (7 << 4) | (15 << 8)>{});
         vm_wait<Sh::NI>(vc);  // V of unit k
-        mfma::fold_pv<D, S>(ms, vc, s_kv[wave], lane, phi, plo);
+        mfma::fold_pv<D, S>(ms, vc, s_kv[wave], lane, pt);
         tile_v(k + 1, vc);
         end_unit(k, info);
         if (held && w == 0 && k + 2 == n_units) look(std::integral_constant<int, 2 * Sh::NI>{});

@@ -305,14 +305,15 @@ __device__ __forceinline__ void partial_rows(const DecodeState<T, D, S>& st, int
 // ---------------------------------------------------------------------------
 // Matrix-core variant of the decode fold (bf16, head_dim 64 or 128).  At D = 64
 // (s = 8, batch 128, 512-2048 tokens) the VALU fold took 140 us, 2.5 TB/s,
-// bound by its vector instructions; this one takes 67 us, 5.2 TB/s.
+// bound by its vector instructions; this one takes 66.6 us, 5.2 TB/s (66.1
+// with weights in two parts).
 //
 // The s query heads of a group are the columns of a 16-wide MFMA tile (padded
 // with zero queries), the 16 tokens of a page its rows:
 //   S^T[token][head] = K . Q^T   D / 32 x v_mfma_f32_16x16x32_bf16 (K as the A operand)
-//   O^T[dim][head]  += V^T . P^T D / 16 x v_mfma_f32_16x16x32_bf16 (P split into bf16
-//                                high and low parts for fp32-level accuracy;
-//                                the k dimension holds 4 tokens x {hi, lo})
+//   O^T[dim][head]  += V^T . P^T D / 16 x v_mfma_f32_16x16x32_bf16 (P as the sum of two
+//                                bf16 parts, the k dimension holding 4 tokens
+//                                x 2 parts; at D = 64 a third part follows)
 // Lane l owns head column l % 16 and tokens 4 (l / 16) .. +3 of every tile, so
 // the softmax state and the rescale stay in the lane.  The wave stages each
 // tile through its own 64 D bytes of LDS, K and V with 16-byte chunks XOR-swizzled
@@ -372,32 +373,52 @@ __device__ __forceinline__ void begin_item(State<D, S>& st, const uint16_t* q_gr
   reset<D, S>(st);
 }
 
-// Split four fp32 softmax weights into bf16 high parts (round to nearest
-// even) and bf16 low parts (the rounding residue, exact in fp32): hi + lo
-// carries ~16 mantissa bits, so the PV product keeps fp32-level accuracy
-// while both halves run on the bf16 matrix cores.  Conversions are gfx950's
-// v_cvt_pk_bf16_f32 (two values per instruction, nearest even).
-__device__ __forceinline__ void split_hi_lo(const float (&p)[4], s16x4_t& hi, s16x4_t& lo) {
+// Four fp32 softmax weights as sums of N bf16 parts: each part is what the
+// parts before it leave (exact in fp32), rounded to nearest even.  Two parts
+// carry ~16 bits of a weight, three all 24.  head_dim 64 takes three: its
+// weights were fp32 on the VALU before they ran on the matrix cores.
+// Conversions are gfx950's v_cvt_pk_bf16_f32 (two values per instruction).
+template <int D> constexpr int kParts = D == 64 ? 3 : 2;
+template <int N>
+struct Weights {
+  s16x4_t part[N];
+};
+template <int N>
+__device__ __forceinline__ void split_parts(const float (&p)[4], Weights<N>& w) {
   typedef float f32x2_t __attribute__((ext_vector_type(2)));
   typedef __bf16 bf16x2v_t __attribute__((ext_vector_type(2)));
-  const f32x2_t p01 = f32x2_t{p[0], p[1]}, p23 = f32x2_t{p[2], p[3]};
-  const bf16x2v_t h01 = __builtin_convertvector(p01, bf16x2v_t);
-  const bf16x2v_t h23 = __builtin_convertvector(p23, bf16x2v_t);
-  const bf16x2v_t l01 = __builtin_convertvector(p01 - __builtin_convertvector(h01, f32x2_t), bf16x2v_t);
-  const bf16x2v_t l23 = __builtin_convertvector(p23 - __builtin_convertvector(h23, f32x2_t), bf16x2v_t);
-  // whole-vector bit casts only (a bit cast of one vector element misreads)
-  hi = __builtin_bit_cast(s16x4_t, u32x2_t{__builtin_bit_cast(uint32_t, h01), __builtin_bit_cast(uint32_t, h23)});
-  lo = __builtin_bit_cast(s16x4_t, u32x2_t{__builtin_bit_cast(uint32_t, l01), __builtin_bit_cast(uint32_t, l23)});
+  f32x2_t p01 = f32x2_t{p[0], p[1]}, p23 = f32x2_t{p[2], p[3]};
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const bf16x2v_t h01 = __builtin_convertvector(p01, bf16x2v_t);
+    const bf16x2v_t h23 = __builtin_convertvector(p23, bf16x2v_t);
+    p01 -= __builtin_convertvector(h01, f32x2_t);
+    p23 -= __builtin_convertvector(h23, f32x2_t);
+    // whole-vector bit casts only (a bit cast of one vector element misreads)
+    w.part[i] =
+        __builtin_bit_cast(s16x4_t, u32x2_t{__builtin_bit_cast(uint32_t, h01), __builtin_bit_cast(uint32_t, h23)});
+  }
 }
 
-// acc += V^T . (P_hi + P_lo)^T in one 16x16x32 product: the lane's k slots
-// 8 G .. 8 G + 7 carry its 4 tokens twice in A (va = V^T of tokens 4 G + i)
-// and P's high then low parts in B, so the sum over k adds both products.
-__device__ __forceinline__ f32x4_t pv_mfma(const s16x4_t& va, const s16x4_t& phi, const s16x4_t& plo, f32x4_t acc) {
+// acc += V^T . P^T.  The first two parts in one 16x16x32 product: the lane's k
+// slots 8 G .. 8 G + 7 carry its 4 tokens twice in A (va = V^T of tokens
+// 4 G + i) and the two parts in B, so the sum over k adds both products; the
+// third, where there is one, beside zeros in another.  (A 16x16x16 product would
+// do for it, but one that accumulates on a 16x16x32 product's result, as compiled
+// here, gave wrong sums.)
+template <int N>
+__device__ __forceinline__ f32x4_t pv_mfma(const s16x4_t& va, const Weights<N>& w, f32x4_t acc) {
+  static_assert(N == 2 || N == 3, "parts");
   const s16x8_t a = __builtin_shufflevector(va, va, 0, 1, 2, 3, 0, 1, 2, 3);
-  const s16x8_t b = __builtin_shufflevector(phi, plo, 0, 1, 2, 3, 4, 5, 6, 7);
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), acc,
-                                                 0, 0, 0);
+  const s16x8_t b = __builtin_shufflevector(w.part[0], w.part[1], 0, 1, 2, 3, 4, 5, 6, 7);
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), acc,
+                                                0, 0, 0);
+  if constexpr (N == 3) {
+    const s16x8_t c = __builtin_shufflevector(w.part[2], s16x4_t{0, 0, 0, 0}, 0, 1, 2, 3, 4, 5, 6, 7);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, c), acc,
+                                                  0, 0, 0);
+  }
+  return acc;
 }
 
 // The fold of one tile in two halves, so that a tile's V loads can be waited
@@ -405,11 +426,11 @@ __device__ __forceinline__ f32x4_t pv_mfma(const s16x4_t& va, const s16x4_t& phi
 // chunk l mod D/8 of token l / (D/8) + 512/D i); lds: this wave's staging (K
 // then V); valid: live tokens of the tile.
 //
-// fold_qk: K to LDS, S^T = K . Q^T, online softmax; the P^T operands (bf16
-// high and low parts of the lane's 4 weights) come back in phi / plo.
+// fold_qk: K to LDS, S^T = K . Q^T, online softmax; the P^T operands (the bf16
+// parts of the lane's 4 weights) come back in pt.
 template <int D, int S>
 __device__ __forceinline__ void fold_qk(State<D, S>& st, const u32x4 (&k)[D / 32], uint8_t* lds, int lane, int valid,
-                                        float scale_log2, s16x4_t& phi, s16x4_t& plo) {
+                                        float scale_log2, Weights<kParts<D>>& pt) {
   constexpr int TPI = 512 / D;  // tokens per wave-wide load
   const int G = lane >> 4, p = lane & 15, tok = lane / (D / 8), chunk = lane % (D / 8);
 #pragma unroll
@@ -444,14 +465,14 @@ __device__ __forceinline__ void fold_qk(State<D, S>& st, const u32x4 (&k)[D / 32
 #pragma unroll
   for (int i = 0; i < 4; ++i) pw[i] = fast_exp2(fmaf(x[i], scale_log2, -st.m));
   st.l += (pw[0] + pw[1]) + (pw[2] + pw[3]);
-  split_hi_lo(pw, phi, plo);
+  split_parts(pw, pt);
 }
 
 // fold_pv: V to LDS, O^T += V^T . P^T; lane p of group G addresses token
 // 4 G + p / 4, dims 16 mb + 4 (p % 4).
 template <int D, int S>
 __device__ __forceinline__ void fold_pv(State<D, S>& st, const u32x4 (&v)[D / 32], uint8_t* lds, int lane,
-                                        const s16x4_t& phi, const s16x4_t& plo) {
+                                        const Weights<kParts<D>>& pt) {
   constexpr int TPI = 512 / D;  // tokens per wave-wide load
   const int G = lane >> 4, p = lane & 15, tok = lane / (D / 8), chunk = lane % (D / 8);
 #pragma unroll
@@ -462,7 +483,7 @@ __device__ __forceinline__ void fold_pv(State<D, S>& st, const u32x4 (&v)[D / 32
     const int d = mb * 16 + 4 * (p & 3);
     const lds_s16x4_t* src = (const lds_s16x4_t*)(lds + kTileBytes<D> + swz_v<D>(vtok, d >> 3) + (d & 7) * 2);
     const s16x4_t va = __builtin_amdgcn_ds_read_tr16_b64_v4i16(const_cast<lds_s16x4_t*>(src));
-    st.acc[mb] = pv_mfma(va, phi, plo, st.acc[mb]);
+    st.acc[mb] = pv_mfma(va, pt, st.acc[mb]);
   }
 }
 
@@ -470,9 +491,9 @@ __device__ __forceinline__ void fold_pv(State<D, S>& st, const u32x4 (&v)[D / 32
 template <int D, int S>
 __device__ __forceinline__ void fold(State<D, S>& st, const u32x4 (&k)[D / 32], const u32x4 (&v)[D / 32], uint8_t* lds, int lane,
                                      int valid, float scale_log2) {
-  s16x4_t phi, plo;
-  fold_qk<D, S>(st, k, lds, lane, valid, scale_log2, phi, plo);
-  fold_pv<D, S>(st, v, lds, lane, phi, plo);
+  Weights<kParts<D>> pt;
+  fold_qk<D, S>(st, k, lds, lane, valid, scale_log2, pt);
+  fold_pv<D, S>(st, v, lds, lane, pt);
 }
 
 // Totals of the head column of this lane: L summed over the 4 lane groups.
@@ -491,8 +512,12 @@ __device__ __forceinline__ void finish(const State<D, S>& st, int lane, T* out) 
 #pragma unroll
     for (int mb = 0; mb < D / 16; ++mb) {
       const int d = mb * 16 + 4 * G;
-      const uint32_t lo = (uint32_t)f32_to_bf16(st.acc[mb][0] * inv) | (uint32_t)f32_to_bf16(st.acc[mb][1] * inv) << 16;
-      const uint32_t hi = (uint32_t)f32_to_bf16(st.acc[mb][2] * inv) | (uint32_t)f32_to_bf16(st.acc[mb][3] * inv) << 16;
+      // (head_dim 64 divides, as its VALU fold did)
+      f32x4_t o;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = D == 64 ? st.acc[mb][i] / L : st.acc[mb][i] * inv;
+      const uint32_t lo = (uint32_t)f32_to_bf16(o[0]) | (uint32_t)f32_to_bf16(o[1]) << 16;
+      const uint32_t hi = (uint32_t)f32_to_bf16(o[2]) | (uint32_t)f32_to_bf16(o[3]) << 16;
       *reinterpret_cast<uint2*>(out + n * D + d) = make_uint2(lo, hi);
     }
   }
