@@ -379,6 +379,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
   mfma::State<D, S> ms;  // matrix-core variant (bf16)
   auto& s_kv = sm.kv;
   bool head_partial = false;
+  int first_unit = 0;  // of the present item, in this range
 
   // Element offset and live tokens of unit k's tile for this wave (a null
   // tile past the range); the trace instantiation records the tile's rows.
@@ -482,6 +483,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
       info = __builtin_amdgcn_readfirstlane(s_info[k]);
       if (info_start(info) || k == 0) {
         head_partial = !info_start(info);
+        first_unit = k;
         const int g = info_hb(info) * W + w;
         const T* qg = qbase + ((int64_t)info_row(info) * a.H_q + (int64_t)g * S) * D;
         if constexpr (MF) {
@@ -500,6 +502,59 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
       }
     }
     return info;
+  };
+  // At head_dim 64, the matrix-core state of an item's part that is not finite
+  // is made again from the part's units (first_unit .. k) with the VALU fold, as
+  // every part was before: V . (p1 + p2 + p3) is NaN for an infinite V whose
+  // weight needs fewer parts, and weights up to 2^kRescaleSlack overflow sooner.
+  // One head at a time, so that this rare path holds few registers.
+  constexpr bool kRedo = MF && D == 64;
+  auto not_finite = [&]() {
+    bool odd = !(fabsf(ms.l) <= __FLT_MAX__);
+#pragma unroll
+    for (int mb = 0; mb < D / 16; ++mb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) odd |= !(fabsf(ms.acc[mb][i]) <= __FLT_MAX__);
+    return __builtin_amdgcn_ballot_w64(odd && (lane & 15) < S) != 0;
+  };
+  auto redo = [&](int k) {
+    const int info = __builtin_amdgcn_readfirstlane(s_info[k]);
+    const T* qg = qbase + ((int64_t)info_row(info) * a.H_q + (int64_t)(info_hb(info) * W + w) * S) * D;
+    const int n = lane & 15, Gl = lane >> 4;
+#pragma unroll 1
+    for (int j = 0; j < S; ++j) {
+      using Sh1 = DecodeShape<T, D, 1>;
+      DecodeState<T, D, 1> s1;
+      s1.q[0] = *reinterpret_cast<const u32x4*>(qg + j * D + dl * Sh1::VEC);
+      s1.m[0] = kMInit;
+      s1.l[0] = 0.0f;
+#pragma unroll
+      for (int e = 0; e < Sh1::VEC; ++e) s1.o[0][e] = 0.0f;
+#pragma unroll 1
+      for (int u = first_unit; u <= k; ++u) {
+        int64_t off;
+        int valid;
+        unit_tile(u, off, valid, false);
+        u32x4 kr[Sh1::NI], vr[Sh1::NI];
+        issue_tile<Sh1::NI>(tile_rsrc<T, D>(kp + off, valid), tile_rsrc<T, D>(vp + off, valid), lane_off, kr, vr);
+        fold_tile<T, D, 1>(s1, kr, vr, row, valid, a.scale_log2);
+      }
+      float M[1], L[1], O[1][Sh1::VEC];
+      merge_rows<T, D, 1>(s1, M, L, O);
+      // lane (n = j, Gl) takes dims 16 mb + 4 Gl + i, from the lane of those dims
+#pragma unroll
+      for (int mb = 0; mb < D / 16; ++mb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int from = (16 * mb + 4 * Gl) / Sh1::VEC;
+          const float even = __shfl(O[0][i], from), odd = __shfl(O[0][(4 + i) % Sh1::VEC], from);
+          if (n == j) ms.acc[mb][i] = Gl & 1 ? odd : even;
+        }
+      if (n == j) {
+        ms.m = M[0];
+        ms.l = Gl == 0 ? L[0] : 0.0f;
+      }
+    }
   };
   // End of unit k (k < n_units): an item that ends here is finished in place
   // when it lies wholly in the range; a part cut by the range stores its
@@ -633,6 +688,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
         const int info = __builtin_amdgcn_readfirstlane(s_info[k]);
         if (info_start(info) || k == 0) {
           head_partial = !info_start(info);
+          first_unit = k;
           mfma::reset<D, S>(ms);
         }
         vm_wait<Sh::NI>(kc);  // K of unit k and the queries (issued before it)
@@ -656,6 +712,15 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
         vm_wait<Sh::NI>(vc);  // V of unit k
         mfma::fold_pv<D, S>(ms, vc, s_kv[wave], lane, pt);
         tile_v(k + 1, vc);
+        if constexpr (kRedo) {
+          if ((info_end(info) || k == n_units - 1) && not_finite()) {
+            vm_wait<0>(kc);  // (all loads, before their registers may move)
+            vm_wait<0>(vc);
+            vm_wait<0>(ms.qt);
+            vm_wait<0>(ctr);
+            redo(k);
+          }
+        }
         end_unit(k, info);
         if (held && w == 0 && k + 2 == n_units) look(std::integral_constant<int, 2 * Sh::NI>{});
       } while (++k < n_units);
@@ -689,6 +754,9 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
             mfma::fold<D, S>(ms, kr[u], vr[u], s_kv[wave], lane, info_valid(info), a.scale_log2);
           else
             fold_tile<T, D, S>(st, kr[u], vr[u], row, info_valid(info), a.scale_log2);
+          if constexpr (kRedo) {
+            if ((info_end(info) || k == n_units - 1) && not_finite()) redo(k);
+          }
           end_unit(k, info);
         }
       }
