@@ -261,15 +261,20 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
     const bool all_cus = dims->dtype != PA_BF16 || dims->head_dim != 128 || p.W < 8;
     const int teams = pa::stream_teams(p.W);
     const int64_t g_min_teams = (p.u_max + pa::kStreamMaxUnits / teams - 1) / (pa::kStreamMaxUnits / teams);
+    // The last choice, where the fixed scratch holds none of the others, is one
+    // workgroup on each of 13/16 of the CUs: how many fit a CU depends on a
+    // kernel's registers and LDS, and what the no-allocation entry accepts
+    // should not.
     struct Choice {
       int sub;
-      bool all;
+      bool all, fill;  // every CU; as many workgroups as fit each
     };
-    for (const Choice c : {Choice{teams, all_cus}, Choice{1, all_cus}, Choice{1, false}}) {
+    for (const Choice c : {Choice{teams, all_cus, true}, Choice{1, all_cus, true}, Choice{1, false, true},
+                           Choice{1, false, false}}) {
       const int64_t least = c.sub > 1 ? (g_min_teams + c.sub - 1) / c.sub : p.g_min;  // workgroups
       const int64_t most = pa::kStreamMaxGrid / c.sub;
       if (c.sub > 1 && least > most) continue;
-      const int per_cu = pa::stream_occupancy(dims->dtype, dims->head_dim, p.s, p.W, c.sub);
+      const int per_cu = c.fill ? pa::stream_occupancy(dims->dtype, dims->head_dim, p.s, p.W, c.sub) : 1;
       if (per_cu <= 0) return PA_EHIP;
       int64_t g = (int64_t)per_cu * cus * (c.all ? 1 : kStreamCuNum) / (c.all ? 1 : kStreamCuDen);
       if (g < 1) g = 1;

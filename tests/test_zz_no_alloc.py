@@ -88,3 +88,29 @@ def test_noalloc_rejects_calls_beyond_the_scratch():
     torch.cuda.synchronize()
     assert rc == pb.PA_ENOSPC
     assert bool((out == 7.0).all())
+
+
+@pytest.mark.parametrize("D,s", [(64, 1), (64, 2), (64, 8), (128, 2), (128, 6)])
+def test_noalloc_takes_a_call_whose_partials_leave_room_for_one_workgroup_per_cu(D, s):
+    """fp32 chunk rows whose split partials leave the fixed scratch room for one
+    stream workgroup on each of 13/16 of the CUs and not for two: accepted
+    however many workgroups of the kernel fit a CU."""
+    import torch
+    H_kv, slots, rec = 8, 16, s * (D + 2) * 4  # declared contexts of 16 splits; a record's bytes
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    stream = cus * 13 // 16 * H_kv * (2 * rec + 8) + 3 * 256
+    rows = ((32 << 20) - stream - 2 * 256) // (H_kv * slots * rec)
+    assert rows * H_kv * slots * rec + 2 * stream > 32 << 20
+    announce(f"no-alloc entry: fp32 D={D} s={s}, {rows} chunk rows at the scratch limit")
+    b = W.generate("tiny", seed=D + s, dtype="fp32", overrides=dict(H_q=s * H_kv, H_kv=H_kv, D=D, ctx=("list", [rows, 50]),
+                                                                    pool=("factor", 1.2)))
+    q = W._fill_normal((rows, s * H_kv, D), 3, "q", 1.0, "fp32", 1)
+    table = np.zeros((2, slots * 128), np.int32)
+    table[:, :b.block_table.shape[1]] = b.block_table
+    b = W.Batch(**{**b.__dict__, "q": q, "block_table": table, "query_start_loc": np.array([0, rows - 1, rows], np.int32)})
+    dev = upload(b)
+    out = torch.full_like(dev["q"], float("nan"))
+    dims = pb.make_dims(dev["q"], dev["k"], dev["bt"], slots * 2048, num_q_rows=rows, max_q_len=rows - 1)
+    pb.paged_attn_varlen_noalloc(dev["q"], dev["k"], dev["v"], dev["bt"], dev["cl"], dev["qsl"], b.scale, out, dims)
+    torch.cuda.synchronize()
+    assert_parity(out.cpu().numpy(), run_oracle(b), strict=False, what="at the scratch limit")
