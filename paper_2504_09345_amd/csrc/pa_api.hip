@@ -306,6 +306,8 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
     sa.H_kv = dims->num_kv_heads;
     sa.max_context_len = dims->max_context_len;
     sa.nb = p.nb;
+    // (max_q_len says that there is no longer chunk, so no chunk kernel runs)
+    sa.chunk_rows = varlen && !p.prefill && pa::prefill_supported(dims->dtype, dims->head_dim, p.s) ? p.rows : 0;
     sa.trace = trace;
   }
   if (p.st_o + p.st_ml + p.st_cum + p.sp_o + p.sp_ml > workspace_bytes) return PA_ENOSPC;

@@ -69,6 +69,7 @@ struct StreamArgs {
   float scale_log2;
   int B, H_q, H_kv, max_context_len;
   int nb;            // head blocks = H_kv / W
+  int chunk_rows;    // query rows of a call without a chunk kernel whose longer chunks are taken too, else 0
   // Gather trace (nullptr in attention calls): [H_kv][B][bt_stride * 16]
   // int64, the pool row ((page * H_kv + g) * 16 + slot) each loaded token came
   // from; launched through the trace instantiations of the kernels.

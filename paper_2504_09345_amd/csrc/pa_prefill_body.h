@@ -482,29 +482,9 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
       if (__builtin_amdgcn_ballot_w64(odd) != 0 && lane == 0) sm.vwide = 1;
       __syncthreads();
       if (sm.vwide) {
-        using Sh = DecodeShape<uint16_t, D, S>;
-        const int dl = lane % Sh::LPT, row = lane / Sh::LPT;
         for (int p = w; p < npos; p += kPfWaves) {
-          DecodeState<uint16_t, D, S> st;
           const int64_t at = ((int64_t)(q0 + pos0 + p) * a.H_q + (int64_t)g * S) * D;
-#pragma unroll
-          for (int j = 0; j < S; ++j) {
-            st.q[j] = *reinterpret_cast<const u32x4*>(qg + at + j * D + dl * Sh::VEC);
-            st.m[j] = kMInit;
-            st.l[j] = 0.0f;
-#pragma unroll
-            for (int e = 0; e < Sh::VEC; ++e) st.o[j][e] = 0.0f;
-          }
-          const int keys = lim0 + p + 1;
-          for (int pg = 0; pg * kPage < keys; ++pg) {
-            const int64_t tile = tile_offset(__builtin_amdgcn_readfirstlane(bt.page(b, pg)), g, a.H_kv, D);
-            const int valid = min(kPage, keys - pg * kPage);
-            u32x4 kr[Sh::NI], vr[Sh::NI];
-            issue_tile<Sh::NI>(tile_rsrc<uint16_t, D>(kp + tile, valid), tile_rsrc<uint16_t, D>(vp + tile, valid),
-                               lane * 16, kr, vr);
-            fold_tile<uint16_t, D, S>(st, kr, vr, row, valid, a.scale_log2);
-          }
-          finish_rows<uint16_t, D, S>(st, row, dl, og + at);
+          attend_row<uint16_t, D, S>(qg + at, kp, vp, bt, b, g, a.H_kv, lim0 + p + 1, a.scale_log2, lane, og + at);
         }
         continue;
       }

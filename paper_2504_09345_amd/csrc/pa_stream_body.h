@@ -290,15 +290,20 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
   int32_t* s_page = tm.page;
   int32_t* s_info = tm.info;
   const int R = a.B;  // items are sequences
+  // bf16, head_dim 128: what the chunk kernel took before decode-only calls ran
+  // without it
+  constexpr bool kChunkRows = MF && D == 128 && SPLIT;
 
   // 1. pages per sequence and their prefix sums (every workgroup, redundantly)
   {
     const int per = (R + NT - 1) / NT;
     const int r0 = min(R, tid * per), r1 = min(R, r0 + per);
     int local = 0;
+    bool chunks = false;
     for (int r = r0; r < r1; ++r) {
       int row, nv;
       const int status = seq_decode_row(a.query_start_loc, a.context_lens, a.max_context_len, r, row, nv);
+      if constexpr (kChunkRows) chunks |= status == 0 && a.chunk_rows > 0 && a.query_start_loc[r + 1] > row + 1;
       int np = status == 1 ? (nv + kPage - 1) / kPage : 0;
       const bool bad = status < 0 || np > (int)a.bt_stride;  // contract violation: a NaN row (below)
       if (bad) np = 0;
@@ -311,6 +316,33 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
     const int off = block_exclusive_scan<NT>(local, s_scan);
     for (int r = r0; r < r1; ++r) s_cum[r] += off;
     if (tid == NT - 1) s_cum[R] = off + local;
+    if constexpr (kChunkRows) {
+      // Chunks that the call's max_q_len does not allow, and for which no chunk
+      // kernel was launched: the wave that met one takes this workgroup's share
+      // of its rows, one (row, query head) after the other.
+      for (uint64_t met = __builtin_amdgcn_ballot_w64(chunks); met != 0; met &= met - 1) {
+        const int c0 = __builtin_amdgcn_readlane(r0, __builtin_ctzll(met));
+        const int c1 = __builtin_amdgcn_readlane(r1, __builtin_ctzll(met));
+        for (int r = c0; r < c1; ++r) {
+          const int q0 = a.query_start_loc[r], L = a.query_start_loc[r + 1] - q0, C = a.context_lens[r];
+          if (L < 2) continue;
+          const bool bad = C > a.max_context_len || L > C || (C + kPage - 1) / kPage > (int)a.bt_stride;
+          for (int i = wg; i < L * a.H_q; i += n_wg) {
+            const int j = i / a.H_q, h = i - j * a.H_q;
+            if (q0 + j < 0 || q0 + j >= a.chunk_rows) continue;
+            const int64_t at = ((int64_t)(q0 + j) * a.H_q + h) * D;
+            T* o = reinterpret_cast<T*>(a.out) + at;
+            if (bad)
+              for (int e = lane; e < D; e += 64) store_out<T>(o + e, NAN);
+            else
+              attend_row<T, D, 1>(reinterpret_cast<const T*>(a.q) + at, reinterpret_cast<const T*>(a.k_pages),
+                                  reinterpret_cast<const T*>(a.v_pages), BlockTable{a.block_table, a.bt_stride}, r,
+                                  h / S, a.H_kv, C - L + j + 1, a.scale_log2, lane, o,
+                                  TR ? a.trace + ((int64_t)(h / S) * R + r) * (a.bt_stride * kPage) : nullptr);
+          }
+        }
+      }
+    }
     __syncthreads();
   }
   const int U = a.nb * s_cum[R];

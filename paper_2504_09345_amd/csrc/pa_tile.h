@@ -273,6 +273,37 @@ __device__ __forceinline__ void finish_rows(const DecodeState<T, D, S>& st, int 
   }
 }
 
+// One query row of sequence b, alone in its wave: the S query heads at q
+// ([S][D]) over the first `keys` keys of KV head g, a page after the other, to
+// out (for rows that the fast paths cannot take).  trace: nullptr, or the gather
+// trace's entry of token 0.
+template <typename T, int D, int S>
+__device__ __forceinline__ void attend_row(const T* q, const T* kp, const T* vp, const BlockTable& bt, int b, int g,
+                                           int H_kv, int keys, float scale_log2, int lane, T* out,
+                                           int64_t* trace = nullptr) {
+  using Sh = DecodeShape<T, D, S>;
+  const int dl = lane % Sh::LPT, row = lane / Sh::LPT;
+  DecodeState<T, D, S> st;
+#pragma unroll
+  for (int j = 0; j < S; ++j) {
+    st.q[j] = *reinterpret_cast<const u32x4*>(q + j * D + dl * Sh::VEC);
+    st.m[j] = kMInit;
+    st.l[j] = 0.0f;
+#pragma unroll
+    for (int e = 0; e < Sh::VEC; ++e) st.o[j][e] = 0.0f;
+  }
+#pragma unroll 1
+  for (int pg = 0; pg * kPage < keys; ++pg) {
+    const int64_t tile = tile_offset(__builtin_amdgcn_readfirstlane(bt.page(b, pg)), g, H_kv, D);
+    const int valid = min(kPage, keys - pg * kPage);
+    if (trace != nullptr && lane < valid) trace_put(trace, pg * kPage + lane, tile / D + lane);
+    u32x4 kr[Sh::NI], vr[Sh::NI];
+    issue_tile<Sh::NI>(tile_rsrc<T, D>(kp + tile, valid), tile_rsrc<T, D>(vp + tile, valid), lane * 16, kr, vr);
+    fold_tile<T, D, S>(st, kr, vr, row, valid, scale_log2);
+  }
+  finish_rows<T, D, S>(st, row, dl, out);
+}
+
 // Partial record of one item: unnormalised O in 16-byte chunks (head c / (D /
 // 4), dims 4 (c mod D / 4) .. +3 of chunk c: [S][D]), then (M, L) per head.
 template <int D, int S>
