@@ -321,7 +321,9 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
   const int64_t chunk_rows = (int64_t)dims->num_q_rows - dims->num_seqs;
   // Every sequence carrying max_q_len > 1 rows (the rows add up to
   // num_seqs * max_q_len) leaves no decode row: the stream-K kernel, which
-  // takes only one-row sequences, would find no work and is not launched.
+  // takes only one-row sequences, would find no work and is not launched (a
+  // single row that is there all the same is a chunk of one to the prefill
+  // kernel).
   const bool no_decode_rows = p.prefill && dims->max_q_len > 1 &&
                               (int64_t)dims->max_q_len * dims->num_seqs == dims->num_q_rows;
   const bool launch_stream = p.stream && dims->num_seqs > 0 && !no_decode_rows;
@@ -363,6 +365,7 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
     pf.H_q = dims->num_q_heads;
     pf.H_kv = dims->num_kv_heads;
     pf.max_context_len = dims->max_context_len;
+    pf.min_rows = launch_stream ? 2 : 1;
     pf.trace = trace;
     if (mixed) {
       // a quarter of the CUs for the chunks, the rest (at most the decode

@@ -118,8 +118,8 @@ int stream_occupancy(int dtype, int D, int s, int W, int sub);  // workgroups pe
 // translation unit per combination, compiled in parallel).
 template <typename T, int D, bool TR> const void* stream_pick(int s, int W, int sub);
 
-// Arguments of the MFMA chunked-prefill kernel (bf16): the rows
-// of every sequence with a chunk of L > 1 query rows.
+// Arguments of the MFMA chunked-prefill kernel (bf16): the rows of every
+// sequence with a chunk of L >= min_rows query rows.
 struct PrefillArgs {
   const void* q;
   const void* k_pages;
@@ -131,6 +131,7 @@ struct PrefillArgs {
   int64_t bt_stride;
   float scale_log2;
   int B, H_q, H_kv, max_context_len;
+  int min_rows;  // sequences of at least this many rows are taken: 2, or 1 where no stream kernel runs
   int64_t* trace;  // gather-trace launches only (see StreamArgs), else nullptr
 };
 

@@ -70,8 +70,9 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int B = a.B;
 
-  // items per sequence: ceil(L / PB) * H_kv for chunks (L > 1), else 0;
-  // s_cum[b] = items of sequences before b
+  // items per sequence: ceil(L / PB) * H_kv for chunks (L >= min_rows: 1 where
+  // no stream kernel takes the single rows), else 0; s_cum[b] = items of
+  // sequences before b
   {
     const int per = (B + kPfThreads - 1) / kPfThreads;
     const int b0 = min(B, tid * per), b1 = min(B, b0 + per);
@@ -79,7 +80,7 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
     for (int b = b0; b < b1; ++b) {
       const int L = a.query_start_loc[b + 1] - a.query_start_loc[b];
       s_cum[b] = local;
-      local += L > 1 ? ((L + PB - 1) / PB) * a.H_kv : 0;
+      local += L >= a.min_rows ? ((L + PB - 1) / PB) * a.H_kv : 0;
     }
     const int off = block_exclusive_scan<kPfThreads>(local, s_scan);
     for (int b = b0; b < b1; ++b) s_cum[b] += off;

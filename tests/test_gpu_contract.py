@@ -1,6 +1,7 @@
 """Varlen calls whose dims do not match query_start_loc, outside the contract
 but answered before the kernels were routed by those dims: a chunk longer than a
-max_q_len of 1.  All buffers hold every row that query_start_loc names."""
+max_q_len of 1, and a single row where every sequence should have max_q_len
+rows.  All buffers hold every row that query_start_loc names."""
 import numpy as np
 import pytest
 import torch
@@ -48,3 +49,10 @@ def test_longer_chunk_in_a_decode_only_call(s, H_kv):
             want = np.full(got.shape[2], -1)
             want[:C] = (b.block_table[i, t // 16].astype(np.int64) * H_kv + g) * 16 + t % 16
             assert np.array_equal(got[g, i], want)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_single_row_where_every_sequence_should_have_two(D):
+    announce(f"single row beside longer chunks D={D}")
+    b = _batch([1, 3, 2, 1, 3], [50, 70, 2, 1, 400], 4, 8, D, D)
+    assert_parity(_call(b, upload(b), 10, 2), run_oracle(b), strict=False, what="single rows")
