@@ -365,6 +365,7 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
     pf.H_q = dims->num_q_heads;
     pf.H_kv = dims->num_kv_heads;
     pf.max_context_len = dims->max_context_len;
+    pf.rows = dims->num_q_rows;
     pf.min_rows = launch_stream ? 2 : 1;
     pf.trace = trace;
     if (mixed) {

@@ -131,6 +131,7 @@ struct PrefillArgs {
   int64_t bt_stride;
   float scale_log2;
   int B, H_q, H_kv, max_context_len;
+  int rows;      // query rows of the call
   int min_rows;  // sequences of at least this many rows are taken: 2, or 1 where no stream kernel runs
   int64_t* trace;  // gather-trace launches only (see StreamArgs), else nullptr
 };

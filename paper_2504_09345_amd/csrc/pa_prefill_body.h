@@ -121,18 +121,36 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
     const int rem = f - s_cum[b];
     const int g = rem / nblk, jb = rem - g * nblk;
     const int pos0 = jb * PB;                     // first chunk position of the block
-    const int npos = min(PB, L - pos0);           // valid positions in the block
+    int npos = min(PB, L - pos0);                 // valid positions in the block
+    if constexpr (!kF16) {  // no row past the call's, whatever query_start_loc says (as on the split-K kernel)
+      npos = min(npos, a.rows - (q0 + pos0));
+      if (npos <= 0 || q0 < 0) continue;
+    }
     const bool bad = C > a.max_context_len || L > C || (C + kPage - 1) / kPage > (int)a.bt_stride;
 
     __syncthreads();  // previous item's readers of s_k / s_v / s_bt are done
+    const int lim0 = C - L + pos0;                // last key of the block's first row
     if (bad) {  // contract violation: NaN rows, nothing read
-      for (int idx = tid; idx < npos * S * D; idx += kPfThreads) {
-        const int p = idx / (S * D), hd = idx % (S * D);
-        og[((int64_t)(q0 + pos0 + p) * a.H_q + (int64_t)g * S) * D + hd] = 0x7fc0;
+      if constexpr (kF16) {
+        for (int idx = tid; idx < npos * S * D; idx += kPfThreads) {
+          const int p = idx / (S * D), hd = idx % (S * D);
+          og[((int64_t)(q0 + pos0 + p) * a.H_q + (int64_t)g * S) * D + hd] = 0x7fc0;
+        }
+      } else {
+        // (of a chunk longer than its context, the rows that see a key are
+        // computed, as on the split-K kernel)
+        const bool longer = C <= a.max_context_len && (C + kPage - 1) / kPage <= (int)a.bt_stride;
+        for (int p = w; p < npos; p += kPfWaves) {
+          const int64_t at = ((int64_t)(q0 + pos0 + p) * a.H_q + (int64_t)g * S) * D;
+          if (longer && lim0 + p >= 0)
+            attend_row<uint16_t, D, S>(qg + at, kp, vp, bt, b, g, a.H_kv, lim0 + p + 1, a.scale_log2, lane, og + at,
+                                       TR ? a.trace + ((int64_t)g * B + b) * (a.bt_stride * kPage) : nullptr);
+          else
+            for (int i = lane; i < S * D; i += 64) og[at + i] = 0x7fc0;
+        }
       }
       continue;
     }
-    const int lim0 = C - L + pos0;                // last key of the block's first row
     const int npg = (lim0 + npos - 1) / kPage + 1;
     // block-table window: s_bt[p % kPfMaxPages] holds the entry of page p
     for (int i = tid; i < min(npg, kPfMaxPages); i += kPfThreads) s_bt[i] = bt.page(b, i);

@@ -1,7 +1,10 @@
 """Varlen calls whose dims do not match query_start_loc, outside the contract
 but answered before the kernels were routed by those dims: a chunk longer than a
-max_q_len of 1, and a single row where every sequence should have max_q_len
-rows.  All buffers hold every row that query_start_loc names."""
+max_q_len of 1, a single row where every sequence should have max_q_len rows,
+and at head_dim 64 fewer rows than query_start_loc says (chunk rows past
+num_q_rows are not written) and chunks longer than their context (rows that see
+a key are computed, the others NaN).  All buffers hold every row that query_start_loc
+names."""
 import numpy as np
 import pytest
 import torch
@@ -56,3 +59,25 @@ def test_single_row_where_every_sequence_should_have_two(D):
     announce(f"single row beside longer chunks D={D}")
     b = _batch([1, 3, 2, 1, 3], [50, 70, 2, 1, 400], 4, 8, D, D)
     assert_parity(_call(b, upload(b), 10, 2), run_oracle(b), strict=False, what="single rows")
+
+
+@pytest.mark.parametrize("cut", [1, 30, 300])
+def test_rows_past_num_q_rows_are_not_written(cut):
+    announce(f"rows past num_q_rows cut={cut}")
+    rows = [1, 40, 5, 280]
+    b = _batch(rows, [L + 33 for L in rows], 4, 8, 64, cut)
+    n = sum(rows) - cut
+    got = _call(b, upload(b), n, 280)
+    assert np.isnan(got[n:]).all()
+    assert_parity(got[:n], run_oracle(b)[:n], strict=False, what="rows of the call")
+
+
+def test_chunk_longer_than_its_context():
+    announce("D=64 chunk longer than its context")
+    rows, ctx = [9, 20, 2], [5, 120, 1]
+    b = _batch(rows, ctx, 4, 2, 64, 5)
+    got = _call(b, upload(b), sum(rows), 20)
+    keep = np.r_[4:9, 9:29, 30:31]
+    sub = W.Batch(**{**b.__dict__, "q": b.q[keep], "query_start_loc": np.array([0, 5, 25, 26], np.int32)})
+    assert_parity(got[keep], run_oracle(sub), strict=False, what="rows with keys")
+    assert np.isnan(np.delete(got, keep, axis=0)).all()
