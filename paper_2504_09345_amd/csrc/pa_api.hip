@@ -14,6 +14,7 @@
 
 #include "pa_counter.h"
 #include "pa_kernels.h"
+#include "pa_route.h"
 #include "pa_sched.h"
 #include "pagedattn.h"
 
@@ -119,9 +120,8 @@ int plan(const pa_dims_t* d, bool varlen, Plan* p) {
   // max_q_len <= 1: every row is then a decode row, which the stream kernel
   // takes)
   p->split = varlen ? (rows > 0 && !p->prefill && (d->max_q_len > 1 || !p->stream)) : !p->stream;
-  // head_dim 64 chunks took the split-K kernel before the MFMA kernel did: the
-  // workspace stays sized (and a call refused) as if they still do, so that
-  // sizes that callers keep, and what fits the fixed scratch, do not change
+  // head_dim 64 chunks take either kernel, by a rule that needs the CUs (run());
+  // the workspace is sized for both
   const bool sized_as_split = p->split || (p->prefill && d->head_dim != 128 && d->max_q_len > 1);
   p->pps = d->pages_per_split > 0 ? d->pages_per_split : kDefaultPagesPerSplit;
   p->n_split_slots = (int)((max_pages + p->pps - 1) / p->pps);
@@ -230,11 +230,22 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
   hipError_t e = hipSuccess;
   pa::StreamArgs sa{};
   int G = 0, sub = 1;  // workgroups, and ranges of each
-  if (p.stream) {
-    int dev = 0, cus = 0;
+  int cus = 0;
+  if (p.stream || p.prefill) {
+    int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
       return PA_EHIP;
+  }
+  const bool chunks_split =
+      p.prefill && dims->head_dim == 64 &&
+      pa::chunks64_to_split({p.s, dims->num_kv_heads, p.rows, dims->num_seqs, dims->max_q_len, dims->max_context_len},
+                            cus);
+  if (chunks_split) {
+    p.prefill = false;
+    p.split = true;
+  }
+  if (p.stream) {
     // 13/16 of the CUs (208 of 256 on MI355X, 26 per XCD) stream faster than
     // all of them: fewer requests in flight keep HBM in its efficient range.
     // Back-to-back launches (measured as a sustained loop, MI355X): Mixtral
@@ -307,7 +318,8 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
     sa.max_context_len = dims->max_context_len;
     sa.nb = p.nb;
     // (max_q_len says that there is no longer chunk, so no chunk kernel runs)
-    sa.chunk_rows = varlen && !p.prefill && pa::prefill_supported(dims->dtype, dims->head_dim, p.s) ? p.rows : 0;
+    sa.chunk_rows =
+        varlen && !p.prefill && !p.split && pa::prefill_supported(dims->dtype, dims->head_dim, p.s) ? p.rows : 0;
     sa.trace = trace;
   }
   if (p.st_o + p.st_ml + p.st_cum + p.sp_o + p.sp_ml > workspace_bytes) return PA_ENOSPC;
@@ -322,9 +334,9 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
   // Every sequence carrying max_q_len > 1 rows (the rows add up to
   // num_seqs * max_q_len) leaves no decode row: the stream-K kernel, which
   // takes only one-row sequences, would find no work and is not launched (a
-  // single row that is there all the same is a chunk of one to the prefill
-  // kernel).
-  const bool no_decode_rows = p.prefill && dims->max_q_len > 1 &&
+  // single row that is there all the same is a chunk of one to the kernel that
+  // is).
+  const bool no_decode_rows = (p.prefill || chunks_split) && dims->max_q_len > 1 &&
                               (int64_t)dims->max_q_len * dims->num_seqs == dims->num_q_rows;
   const bool launch_stream = p.stream && dims->num_seqs > 0 && !no_decode_rows;
   const bool mixed = launch_stream && p.prefill &&
@@ -347,10 +359,6 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
     if (e != hipSuccess) return PA_EHIP;
   }
   if (p.prefill) {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      return PA_EHIP;
     pa::PrefillArgs pf{};
     pf.q = q;
     pf.k_pages = k_pages;
@@ -404,7 +412,7 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
     a.H_kv = dims->num_kv_heads;
     a.pages_per_split = p.pps;
     a.n_split_slots = p.n_split_slots;
-    a.skip_single_rows = p.stream ? 1 : 0;
+    a.skip_single_rows = launch_stream ? 1 : 0;
     a.trace = trace;
     e = pa::launch_decode(dims->dtype, dims->head_dim, p.s, a, p.rows, stream, next_events());
     if (e != hipSuccess) return PA_EHIP;

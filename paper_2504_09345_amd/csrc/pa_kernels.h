@@ -143,9 +143,7 @@ bool prefill_supported(int dtype, int D, int s);
 bool mixed_supported(int dtype, int D, int s, int W);
 hipError_t launch_mixed(int s, const StreamArgs& sa, const PrefillArgs& pa, int G_dec, int G, hipStream_t st,
                         KernelEvents ev = {});
-// 16-row blocks per wave (2, or 1: twice the items of half the rows) for a call
-// of `rows` query rows in `seqs` sequences on `cus` CUs.
-int prefill_blocks(int s, int H_kv, int rows, int seqs, int cus);
+// blocks: 16-row blocks per wave (prefill_blocks)
 int prefill_occupancy(int D, int s, int blocks, int B);  // workgroups per CU, 0 on error
 hipError_t launch_prefill(int D, int s, int blocks, const PrefillArgs& a, int G, hipStream_t st, KernelEvents ev = {});
 

@@ -88,22 +88,6 @@ static const void* prefill_fn(int D, int s, int blocks, bool trace = false) {
 
 bool prefill_supported(int dtype, int D, int s) { return dtype == 0 && prefill_fn(D, s, kPfBlocksMax) != nullptr; }
 
-// With no more items of 128 rows than CUs, all run at once and the longest
-// item's chain of steps is the call's time: a step with one block per wave has
-// half the products and half the softmax's vector work, at the same staging.
-// 32 query heads over 8: one chunk of 700 rows 31.1 us with 256-row items and
-// 22.5 with 128, 1,000 rows 38.5 and 28.8, 8 of 60-100 rows on 0-1,000 tokens
-// 39.8 and 29.3; one KV head of 8 query heads, 2,048 rows on 1,000 tokens 97.6
-// and 70.4.  Past the line items wait for a second round, or share a CU: one
-// chunk of 1,030 rows 40.5 and 47.5, 1,500 rows 52.7 and 73.3, 2,000 rows on
-// 2,000 tokens 127 and 146, 20 of 60-90 rows on 0-2,000 tokens 69.7 and 87.0.
-// The host knows no lengths: `seqs` chunks of `rows` positions in all have at
-// most this many blocks.
-int prefill_blocks(int s, int H_kv, int rows, int seqs, int cus) {
-  const int pb = pf_rows(1) / s;  // positions per item
-  return ((int64_t)rows + (int64_t)(pb - 1) * seqs) / pb * H_kv <= cus ? 1 : kPfBlocksMax;
-}
-
 int prefill_occupancy(int D, int s, int blocks, int B) {
   const void* fn = prefill_fn(D, s, blocks);
   if (fn == nullptr) return 0;

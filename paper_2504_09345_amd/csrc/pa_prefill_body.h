@@ -4,6 +4,7 @@
 
 #include "pa_device.h"
 #include "pa_kernels.h"
+#include "pa_route.h"
 #include "pa_tile.h"
 
 namespace pa {
@@ -18,12 +19,7 @@ typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 template <bool V> struct PfBool { static constexpr bool value = V; };
 
-constexpr int kPfWaves = 8;
 constexpr int kPfThreads = 64 * kPfWaves;
-// 16-row MFMA blocks per wave, and query rows per item: 256, or 128 for a call
-// that would leave CUs idle with 256 (prefill_blocks)
-constexpr int kPfBlocksMax = 2;
-constexpr int pf_rows(int blocks) { return 16 * blocks * kPfWaves; }
 constexpr int kPfMaxPages = 2048;                  // block-table window in LDS (power of 2)
 constexpr int kPfStepBytes = 8192;                 // K (and V) bytes of a synchronised step
 template <int D> constexpr int kPfStep = kPfStepBytes / (kPage * D * 2);  // its pages: 2 at D = 128, 4 at 64
