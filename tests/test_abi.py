@@ -241,8 +241,8 @@ def test_varlen_all_single_rows_fit_the_sized_workspace(dtype, D):
     rc = pb.load().paged_attn_varlen(FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, 0.088, FAKE, ctypes.byref(d),
                                      FAKE, need, None, None)
     assert rc == pb.PA_EHIP
-    # the same call with chunk rows reserves split-K partials (fp32 / D 64
-    # chunk rows take the per-row kernel)
+    # the same call with chunk rows reserves split-K partials (fp32 chunk rows
+    # take the per-row kernel, head_dim 64 ones may)
     d.num_q_rows, d.max_q_len = 128, 2
     assert pb.pa_workspace_size(d) > need
 

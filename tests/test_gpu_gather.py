@@ -136,9 +136,9 @@ def test_trace_fp32_chunks_take_split_k():
 def test_grid_beyond_resident_workgroups(D):
     """A batch whose declared context bound needs more stream-K ranges than
     the GPU holds at once (2,048 sequences declared up to 8,192 tokens: 512
-    ranges of at most 2,048 units, against one resident workgroup per CU for
-    the matrix-core kernel; D = 64 declares 16,384 tokens for 1,024 ranges
-    against two per CU).  Cut items are merged by whichever part finishes
+    ranges of at most 2,048 units, against one resident workgroup per CU, which
+    is what the matrix-core kernels' LDS allows; D = 64 declares 16,384 tokens
+    for 1,024 ranges, past two per CU as well).  Cut items are merged by whichever part finishes
     last, so the launch completes whatever the residency; trace and output
     are checked."""
     rng = np.random.default_rng(97)

@@ -48,14 +48,19 @@ def test_parts(dtype, D, H_kv, s, pages):
         assert np.array_equal(got.view(np.uint32), again.view(np.uint32)), fill
 
 
-def test_two_cut_items_per_range_and_head_blocks():
-    """Ranges of two or three units that end one item and start the next, with
-    two head blocks per page: both records of a range counted at its end."""
-    announce("two cut items per range")
-    b = W.generate("tiny", seed=3, overrides=dict(H_q=64, H_kv=16, D=128, ctx=("list", [83 + 5 * i for i in range(40)]),
+@pytest.mark.parametrize("first,step", [(83, 5), (20, 4)])
+def test_two_cut_items_per_range_and_head_blocks(first, step):
+    """Ranges of four or five units, and of two or three, that end one item and
+    start the next, with two head blocks per page: both records of a range
+    counted at its end."""
+    announce(f"two cut items per range, contexts from {first}")
+    b = W.generate("tiny", seed=3, overrides=dict(H_q=64, H_kv=16, D=128,
+                                                  ctx=("list", [first + step * i for i in range(40)]),
                                                   pool=("factor", 1.2)))
+    units = 2 * int(((b.context_lens + 15) // 16).sum())
+    assert (4 if first == 83 else 2) <= units / 208 <= (5 if first == 83 else 3)
     dev = upload(b)
-    ws = torch.randint(0, 256, (pb.pa_workspace_size(pb.make_dims(dev["q"], dev["k"], dev["bt"], 278)),),
+    ws = torch.randint(0, 256, (pb.pa_workspace_size(pb.make_dims(dev["q"], dev["k"], dev["bt"], int(b.context_lens.max()))),),
                        dtype=torch.uint8, device="cuda")
     got = _run(b, dev, ws)
     assert_parity(got, run_oracle(b), what="two cut items")
@@ -94,6 +99,32 @@ def test_recorded_launch_replays():
             call()
             torch.cuda.synchronize()
             assert torch.equal(out, ref), f"eager after replay {i}"
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("bf16", 64), ("fp32", 128)])
+@pytest.mark.parametrize("H_kv,s,pages", [(1, 4, 2064), (1, 8, 4100), (2, 1, 3000)])
+def test_parts_in_groups_of_32(dtype, D, H_kv, s, pages):
+    """More than 256 parts (ranges of 8 units, several per workgroup).  The
+    counters that the call left at 0 show the form of its merge: one for the item
+    and one for each group of more than one part."""
+    announce(f"merge in groups of 32: {dtype} D={D} H_kv={H_kv} s={s} pages={pages}")
+    b = W.generate("tiny", seed=pages, dtype=dtype, overrides=dict(
+        H_q=s * H_kv, H_kv=H_kv, D=D, ctx=("list", [16 * pages - 3]), pool=("factor", 1.1)))
+    dev = upload(b)
+    n = pb.pa_workspace_size(pb.make_dims(dev["q"], dev["k"], dev["bt"], 16 * pages))
+    got = None
+    for fill in (0xFF, 0x01, 0xFF):
+        ws = torch.full((n,), fill, dtype=torch.uint8, device="cuda")
+        out = _run(b, dev, ws)
+        counters = int((ws.view(torch.int64) == 0).sum())
+        parts = pages // 8  # on 256 CUs, 1,024 ranges at most
+        assert 256 < parts <= 1024 and counters == parts // 32 + (parts % 32 > 1) + 1
+        if got is None:
+            got = out
+            assert_parity(got, run_oracle(b), strict=False, what=f"{pages} pages")
+        assert np.array_equal(got.view(np.uint32), out.view(np.uint32)), fill
+    for _ in range(2):  # the counters as that call left them
+        assert np.array_equal(got.view(np.uint32), _run(b, dev, ws).view(np.uint32))
 
 
 @pytest.mark.parametrize("pages,low", [(13, 0x3F80), (13, 5), (2, 1), (64, 0x3F80), (64, 7), (208, 5)])

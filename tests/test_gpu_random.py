@@ -44,8 +44,8 @@ def test_random_batch(case):
                        overrides=dict(H_q=s * H_kv, H_kv=H_kv, D=D, prefill=(n_pre, chunk, 0, 700),
                                       decode=(int(rng.integers(0, 20)), 1, 2500), pool=("factor", 1.3)))
     got = run_gpu(b, pages_per_split=pps)
-    # varlen rows of fp32 or D = 64 chunks take the per-row kernel; the MFMA
-    # prefill rows round P and V to fp16 (the strict floor is for decode only)
+    # chunk rows of fp32 and few D = 64 ones take the per-row kernel; the D = 128
+    # MFMA prefill rows round P and V to fp16 (the strict floor is for decode only)
     assert_parity(got, run_oracle(b), strict=not varlen, what=f"case {case}")
 
 

@@ -190,21 +190,25 @@ def test_checker_on_hand_written_paths():
         s_endpgm""") == [None]
 
 
-def test_split_loads_at_head_dim_64():
-    """The same check on the head_dim 64 kernels (their tiles are two loads)."""
+@pytest.mark.parametrize("source", ["pa_stream_small.hip", "pa_trace_small.hip"])
+def test_split_loads_at_head_dim_64(source):
+    """The same check on the head_dim 64 kernels (their tiles are two loads) and
+    their gather-trace instantiations."""
     if not os.path.exists(build.HIPCC):
         pytest.skip("hipcc not available")
-    cmd = [build.HIPCC, *build.FLAGS, "--cuda-device-only", "-S",
-           os.path.join(build.CSRC, "pa_stream_small.hip"), "-o", "-"]
+    cmd = [build.HIPCC, *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", "-"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     kernels = [k for k in _kernels(r.stdout) if "ItLi64E" in k[0]]
     assert kernels
+    counter_loads = 0
     for name, lines, loads in kernels:
         assert loads, name
+        counter_loads += sum(lines[i].startswith("global_load_dwordx2") for i in loads)
         labels = {m.group(1): j for j, l in enumerate(lines) if (m := re.match(r"(\.LBB\w+):", l))}
         for i in sorted(loads):
             m = re.match(r"\w+ v\[(\d+):(\d+)\]", lines[i])
             dst = set(range(int(m.group(1)), int(m.group(2)) + 1))
             t = _untouched(lines, labels, set(loads), i, dst, counted=not lines[i].startswith("global_load"))
             assert t is None, f"{name}: `{t}` touches {lines[i]!r} before its wait"
+    assert counter_loads >= 2 * len(kernels)
