@@ -148,7 +148,8 @@ int paged_attn(const void *q, const void *k_pages, const void *v_pages,
 
 /* Mixed batch: causal prefill chunks and decode rows in one call.  Decode
  * rows take the stream-K kernel; chunk rows (L_b > 1) take an MFMA kernel
- * (bf16) or, otherwise, the per-row split-K kernel.  At head_dim 128 the MFMA
+ * (bf16; not few rows on long contexts at head_dim 64) or, otherwise, the
+ * per-row split-K kernel.  At head_dim 128 the MFMA
  * kernel forms P.V with P rounded to fp16 (relative error 2^-11) and V in
  * fp16 (exact for bf16 magnitudes in [2^-17, 2^16)); a chunk block whose V
  * leaves that range (or holds inf / NaN), or whose output rows have an RMS
@@ -176,10 +177,15 @@ int paged_attn_varlen(const void *q, const void *k_pages, const void *v_pages,
  * the process ends; its address is taken on the first call on each device).
  * The call allocates nothing.
  *   - A call that needs more than the 32 MiB returns PA_ENOSPC and enqueues
- *     nothing.  The stream-K decode rows need 66.5 KiB per workgroup of the
- *     grid at s = 8 (33 KiB at s = 4, 208 workgroups on MI355X: ~7 MB);
- *     fp32 and head_dim 64 chunk rows
- *     need rows x H_q x splits x (D + 2) x 4 bytes.
+ *     nothing.  The stream-K decode rows need W x s x (D + 2) x 8 bytes and 8 W
+ *     for a counter per range of the grid, where W is the largest of 8, 4, 2 and
+ *     1 that divides num_kv_heads (33 KiB at W = 8, s = 4, D = 128).  MI355X
+ *     takes 208 ranges with bf16, head_dim 128 and W = 8 (about 7 MB) and 256 to
+ *     1,024 otherwise, or 208 where the array does not hold those; declared
+ *     contexts of more than 2,048 pages per range in all need more.  Calls with
+ *     chunks at fp32 or head_dim 64 need another rows x H_q x splits x (D + 2) x
+ *     4 bytes (head_dim 64 also where its chunks take the MFMA kernel, which is
+ *     chosen by the GPU's size).
  *   - Every call on one GPU shares that GPU's array and leaves its contents
  *     behind (counters are keyed by call, so nothing needs clearing): calls
  *     that overlap in time on one GPU (other streams, other threads) race on

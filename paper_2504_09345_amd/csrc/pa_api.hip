@@ -103,10 +103,10 @@ int plan(const pa_dims_t* d, bool varlen, Plan* p) {
   p->stream = d->pages_per_split == 0 && d->num_seqs <= pa::kStreamMaxRows && p->nb < 64 &&
               rows < (1 << 19) && p->g_min <= pa::kStreamMaxGrid;
   if (p->stream) {
-    const size_t recs = (size_t)pa::kStreamMaxGrid * 2 * p->W * s;  // (workgroup, slot, wave, head)
+    const size_t recs = (size_t)pa::kStreamMaxGrid * 2 * p->W * s;  // (range, slot, wave, head)
     p->st_o = align256(recs * (size_t)d->head_dim * sizeof(float));
     p->st_ml = align256(recs * 2 * sizeof(float));
-    // arrival counters of cut items: one per (first range, wave)
+    // arrival counters of cut items: the first of each range's W words
     p->st_cum = align256((size_t)pa::kStreamMaxGrid * p->W * sizeof(unsigned long long));
   }
   // chunked-prefill rows of a varlen call: MFMA kernel (bf16)

@@ -61,9 +61,11 @@ struct StreamArgs {
   const int32_t* context_lens;
   const int32_t* query_start_loc;  // nullptr for decode
   void* out;
-  float* ws_o;       // [G][2][W][s][D] partial outputs (slot 0 head, 1 tail)
-  float* ws_ml;      // [G][2][W][s][2]
-  unsigned long long* ws_flag;  // [G][W] arrival counters of cut items (the first of each range's W)
+  // of each range, slot (0: the item that its start cuts, 1: that its end cuts)
+  // and wave:
+  float* ws_o;       // partial outputs, s * D floats (mfma::Record's order, or RowsRecord's [s][D])
+  float* ws_ml;      // (m, l) of the s heads
+  unsigned long long* ws_flag;  // arrival counters of cut items, the first of every W words: one per range
   CounterKey key;               // this call's step of the counters
   int64_t bt_stride;
   float scale_log2;

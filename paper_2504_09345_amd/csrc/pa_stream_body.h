@@ -352,12 +352,12 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
   // small batches, 35 % slower on 8 sequences of 20 to 60 tokens.  Nor does it
   // pay to use the fewest ranges that keep the longest one's length: 8 to 12
   // sequences -13 to +25 %.
-  // Teams beyond the first of each workgroup join once a range has kTeamUnits
+  // Teams beyond the first of each workgroup join once a range has kJoinUnits
   // units: without that bound 8 sequences with 4 KV heads took 33 us against
   // 25 (more parts to merge); with 16 and 32 units, head_dim 64 with one query
   // head per KV head at batch 128 took 25.6 and 38.7 us against 23.
-  constexpr int kTeamUnits = 8;
-  const int G = max(1, SUB == 1 ? min(n_wg, U) : min(n_wg * SUB, max(min(n_wg, U), U / kTeamUnits)));
+  constexpr int kJoinUnits = 8;
+  const int G = max(1, SUB == 1 ? min(n_wg, U) : min(n_wg * SUB, max(min(n_wg, U), U / kJoinUnits)));
   // Rows without units: zeros for an empty decode context, NaN for a contract
   // violation (flagged in s_tail above); rows r = wg (mod n_wg) are this
   // workgroup's to write.
