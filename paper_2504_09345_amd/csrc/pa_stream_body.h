@@ -411,7 +411,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
   mfma::State<D, S> ms;  // matrix-core variant (bf16)
   auto& s_kv = sm.kv;
   bool head_partial = false;
-  int first_unit = 0;  // of the present item, in this range
+  int first_unit = 0;   // of the present item, in this range
+  bool redone = false;  // its state was made again (below)
 
   // Element offset and live tokens of unit k's tile for this wave (a null
   // tile past the range); the trace instantiation records the tile's rows.
@@ -516,6 +517,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
       if (info_start(info) || k == 0) {
         head_partial = !info_start(info);
         first_unit = k;
+        redone = false;
         const int g = info_hb(info) * W + w;
         const T* qg = qbase + ((int64_t)info_row(info) * a.H_q + (int64_t)g * S) * D;
         if constexpr (MF) {
@@ -542,14 +544,17 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
   // One head at a time, so that this rare path holds few registers.
   constexpr bool kRedo = MF && D == 64;
   auto not_finite = [&]() {
-    bool odd = !(fabsf(ms.l) <= __FLT_MAX__);
+    float t[4] = {ms.l, ms.l, ms.l, ms.l};
 #pragma unroll
-    for (int mb = 0; mb < D / 16; ++mb)
+    for (int i = 0; i < 4; ++i) {
+      t[i] *= 0.0f;  // (0, or NaN where a value is infinite or NaN)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) odd |= !(fabsf(ms.acc[mb][i]) <= __FLT_MAX__);
-    return __builtin_amdgcn_ballot_w64(odd && (lane & 15) < S) != 0;
+      for (int mb = 0; mb < D / 16; ++mb) t[i] = fmaf(ms.acc[mb][i], 0.0f, t[i]);
+    }
+    return __builtin_amdgcn_ballot_w64((t[0] + t[1]) + (t[2] + t[3]) != 0.0f && (lane & 15) < S) != 0;
   };
   auto redo = [&](int k) {
+    redone = true;  // (until the next item starts)
     const int info = __builtin_amdgcn_readfirstlane(s_info[k]);
     const T* qg = qbase + ((int64_t)info_row(info) * a.H_q + (int64_t)(info_hb(info) * W + w) * S) * D;
     const int n = lane & 15, Gl = lane >> 4;
@@ -599,7 +604,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
       T* outp = reinterpret_cast<T*>(a.out) + ((int64_t)r * a.H_q + (int64_t)g * S) * D;
       if (!head_partial && !tail_partial) {  // the whole item in this range
         if constexpr (MF)
-          mfma::finish<D, S, T>(ms, lane, outp);
+          mfma::finish<D, S, T>(ms, lane, outp, redone);
         else
           finish_rows<T, D, S>(st, row, dl, outp);
       } else {  // (uniform over the team)
@@ -721,6 +726,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
         if (info_start(info) || k == 0) {
           head_partial = !info_start(info);
           first_unit = k;
+          redone = false;
           mfma::reset<D, S>(ms);
         }
         vm_wait<Sh::NI>(kc);  // K of unit k and the queries (issued before it)

@@ -534,24 +534,38 @@ __device__ __forceinline__ float total_l(const State<D, S>& st) {
 }
 
 // Finish an item in place: out points at head 0 of the group ([s][D]).
+// odd (head_dim 64): a value may be infinite or NaN.
 template <int D, int S, typename T>
-__device__ __forceinline__ void finish(const State<D, S>& st, int lane, T* out) {
+__device__ __forceinline__ void finish(const State<D, S>& st, int lane, T* out, bool odd) {
   const float L = total_l(st);
   const int n = lane & 15, G = lane >> 4;
-  if (n < S) {
-    const float inv = 1.0f / L;
+  auto put = [&](auto value) {
+    if (n < S) {
 #pragma unroll
-    for (int mb = 0; mb < D / 16; ++mb) {
-      const int d = mb * 16 + 4 * G;
-      // (head_dim 64 divides, as its VALU fold did)
-      f32x4_t o;
+      for (int mb = 0; mb < D / 16; ++mb) {
+        const int d = mb * 16 + 4 * G;
+        f32x4_t o;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = D == 64 ? st.acc[mb][i] / L : st.acc[mb][i] * inv;
-      const uint32_t lo = (uint32_t)f32_to_bf16(o[0]) | (uint32_t)f32_to_bf16(o[1]) << 16;
-      const uint32_t hi = (uint32_t)f32_to_bf16(o[2]) | (uint32_t)f32_to_bf16(o[3]) << 16;
-      *reinterpret_cast<uint2*>(out + n * D + d) = make_uint2(lo, hi);
+        for (int i = 0; i < 4; ++i) o[i] = value(st.acc[mb][i]);
+        const uint32_t lo = (uint32_t)f32_to_bf16(o[0]) | (uint32_t)f32_to_bf16(o[1]) << 16;
+        const uint32_t hi = (uint32_t)f32_to_bf16(o[2]) | (uint32_t)f32_to_bf16(o[3]) << 16;
+        *reinterpret_cast<uint2*>(out + n * D + d) = make_uint2(lo, hi);
+      }
+    }
+  };
+  if constexpr (D == 64) {
+    if (odd) {  // wave-uniform
+      put([&](float a) { return a / L; });
+      return;
     }
   }
+  const float inv = 1.0f / L;
+  put([&](float a) {
+    const float o = a * inv;
+    // (head_dim 64 divides, as its VALU fold did: the remainder corrects the
+    // product with the reciprocal to the quotient's rounding)
+    return D == 64 ? fmaf(fmaf(-o, L, a), inv, o) : o;
+  });
 }
 
 // Partial record: unnormalised O in 16-byte chunks in the accumulators' order
