@@ -264,13 +264,19 @@ int run(const void* q, const void* k_pages, const void* v_pages, const int32_t* 
     // the split-K partials (a caller's workspace, sized for kStreamMaxGrid
     // ranges, always holds it; the fixed scratch may hold the smaller grid
     // only).
-    // With fewer than 8 waves per head block, a workgroup holds several teams
-    // with a range each, unless the batch's ranges would overflow the teams'
-    // smaller unit tables: one KV head of 8 query heads at batch 256, 1k-4k
-    // tokens 69 us against 104 with one team; 2 KV heads of one query head,
-    // head_dim 64, batch 276 59 against 84; 4 KV heads, batch 128 66 against 80.
+    // With fewer than 8 waves per head block, a workgroup may hold several teams
+    // with a range each (stream_teams), where the batch is large and its ranges
+    // do not overflow the teams' smaller unit tables.  The line is 8,000 units
+    // (12,000 with 4 waves) by the declared contexts: below it workgroups of one
+    // team are faster.  One team per workgroup and several, on every CU: fp32, one
+    // KV head of 8 query heads, 256 sequences of about 40 tokens (723 units) 21.5
+    // and 27.9 us, of about 700 (10,468) 108 and 73; bf16, head_dim 64, 3 KV heads
+    // of one, 256 of about 40 (2,148) 14.4 and 20.3, of about 700 (30,828) 64 and
+    // 45; fp32, 4 KV heads of 8, 64 of about 40 (172) 15.2 and 23.0, 700 of about
+    // 250 (10,375) 234 and 215.
     const bool all_cus = dims->dtype != PA_BF16 || dims->head_dim != 128 || p.W < 8;
-    const int teams = pa::stream_teams(p.W);
+    const int teams =
+        p.u_max >= (p.W == 4 ? 12000 : 8000) ? pa::stream_teams(dims->dtype, dims->head_dim, p.W) : 1;
     const int64_t g_min_teams = (p.u_max + pa::kStreamMaxUnits / teams - 1) / (pa::kStreamMaxUnits / teams);
     // The last choice, where the fixed scratch holds none of the others, is one
     // workgroup on each of 13/16 of the CUs: how many fit a CU depends on a

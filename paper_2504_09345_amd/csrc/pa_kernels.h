@@ -108,11 +108,14 @@ struct KernelEvents {
   hipEvent_t start = nullptr, stop = nullptr;
 };
 
-// Teams of W waves per stream-K workgroup where W < 8 (a range each): 8 waves
-// per CU keep HBM busy where one team would not.  With one KV head 4 teams, so
-// that the ranges of every CU fit kStreamMaxGrid.
-constexpr int stream_teams(int W) { return W == 1 ? 4 : 8 / W; }
-// sub: 1 or stream_teams(W); G: workgroups (of sub ranges each).
+// Teams of W waves per stream-K workgroup (a range each), 1 where one is as good
+// or better at any size: 8 waves per CU keep HBM busy where fewer would not, but
+// two or three workgroups of one team fit a CU too, and start and end sooner.
+// With one KV head 4 teams, so that the ranges of every CU fit kStreamMaxGrid.
+constexpr int stream_teams(int dtype, int D, int W) {
+  return W == 1 ? 4 : W == 2 && dtype == 0 ? 4 : W == 4 && dtype == 1 && D == 128 ? 2 : 1;
+}
+// sub: 1 or stream_teams(); G: workgroups (of sub ranges each).
 hipError_t launch_stream(int dtype, int D, int s, int W, int sub, const StreamArgs& a, int G, hipStream_t st,
                          KernelEvents ev = {});
 int stream_occupancy(int dtype, int D, int s, int W, int sub);  // workgroups per CU, 0 on error

@@ -353,10 +353,11 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, StreamSmem<W, S
   // pay to use the fewest ranges that keep the longest one's length: 8 to 12
   // sequences -13 to +25 %.
   // Teams beyond the first of each workgroup join once a range has kJoinUnits
-  // units: without that bound 8 sequences with 4 KV heads took 33 us against
-  // 25 (more parts to merge); with 16 and 32 units, head_dim 64 with one query
-  // head per KV head at batch 128 took 25.6 and 38.7 us against 23.
-  constexpr int kJoinUnits = 8;
+  // units (more parts to merge otherwise).  Batches of 4,096 to 8,192 units on one
+  // KV head are 1, 3 and 11 % behind the best grid with bounds of 2, 4 and 8 units,
+  // larger ones (those that teams are used for unless the declared contexts are
+  // far above the real ones) the same with each.
+  constexpr int kJoinUnits = 4;
   const int G = max(1, SUB == 1 ? min(n_wg, U) : min(n_wg * SUB, max(min(n_wg, U), U / kJoinUnits)));
   // Rows without units: zeros for an empty decode context, NaN for a contract
   // violation (flagged in s_tail above); rows r = wg (mod n_wg) are this

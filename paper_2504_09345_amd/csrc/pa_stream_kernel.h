@@ -23,12 +23,12 @@ const void* stream_pick_w(int W, int sub) {
       case 4: return reinterpret_cast<const void*>(&stream_kernel<T, D, S, 4, 1, kStreamRing, mf, TR>);
       case 8: return reinterpret_cast<const void*>(&stream_kernel<T, D, S, 8, 1, kStreamRing, mf, TR>);
     }
-  } else if (sub == stream_teams(W)) {
-    switch (W) {
-      case 1: return reinterpret_cast<const void*>(&stream_kernel<T, D, S, 1, stream_teams(1), kStreamRing, mf, TR>);
-      case 2: return reinterpret_cast<const void*>(&stream_kernel<T, D, S, 2, stream_teams(2), kStreamRing, mf, TR>);
-      case 4: return reinterpret_cast<const void*>(&stream_kernel<T, D, S, 4, stream_teams(4), kStreamRing, mf, TR>);
-    }
+  } else {
+    constexpr int dtype = sizeof(T) == 2 ? 0 : 1;
+    constexpr int n1 = stream_teams(dtype, D, 1), n2 = stream_teams(dtype, D, 2), n4 = stream_teams(dtype, D, 4);
+    if (W == 1 && sub == n1) return reinterpret_cast<const void*>(&stream_kernel<T, D, S, 1, n1, kStreamRing, mf, TR>);
+    if (W == 2 && sub == n2) return reinterpret_cast<const void*>(&stream_kernel<T, D, S, 2, n2, kStreamRing, mf, TR>);
+    if (W == 4 && sub == n4) return reinterpret_cast<const void*>(&stream_kernel<T, D, S, 4, n4, kStreamRing, mf, TR>);
   }
   return nullptr;
 }

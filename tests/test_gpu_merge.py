@@ -101,24 +101,32 @@ def test_recorded_launch_replays():
             assert torch.equal(out, ref), f"eager after replay {i}"
 
 
+# with one range per workgroup, and (past 8,000 units) several of at least 4 units
 @pytest.mark.parametrize("dtype,D", [("bf16", 128), ("bf16", 64), ("fp32", 128)])
-@pytest.mark.parametrize("H_kv,s,pages", [(1, 4, 2064), (1, 8, 4100), (2, 1, 3000)])
-def test_parts_in_groups_of_32(dtype, D, H_kv, s, pages):
-    """More than 256 parts (ranges of 8 units, several per workgroup).  The
-    counters that the call left at 0 show the form of its merge: one for the item
-    and one for each group of more than one part."""
+@pytest.mark.parametrize("H_kv,s,pages,parts", [(1, 4, 2064, 0), (1, 8, 8200, 1024), (2, 1, 8100, 1024)])
+def test_parts_in_groups_of_32(dtype, D, H_kv, s, pages, parts):
+    """More than 256 parts.  What the call wrote shows the form of its merge: a
+    record per part, and a counter left at 0 for the item and for each group of
+    more than one part.  (parts: their number, 0 where it follows from how many
+    workgroups fit a CU.)"""
     announce(f"merge in groups of 32: {dtype} D={D} H_kv={H_kv} s={s} pages={pages}")
     b = W.generate("tiny", seed=pages, dtype=dtype, overrides=dict(
         H_q=s * H_kv, H_kv=H_kv, D=D, ctx=("list", [16 * pages - 3]), pool=("factor", 1.1)))
     dev = upload(b)
     n = pb.pa_workspace_size(pb.make_dims(dev["q"], dev["k"], dev["bt"], 16 * pages))
+    record = H_kv * s * (D + 2) * 4 // 8  # words of a part's record, all its waves
     got = None
     for fill in (0xFF, 0x01, 0xFF):
         ws = torch.full((n,), fill, dtype=torch.uint8, device="cuda")
+        before = ws.view(torch.int64)[0].item()
         out = _run(b, dev, ws)
         counters = int((ws.view(torch.int64) == 0).sum())
-        parts = pages // 8  # on 256 CUs, 1,024 ranges at most
-        assert 256 < parts <= 1024 and counters == parts // 32 + (parts % 32 > 1) + 1
+        n_parts, rest = divmod(int((ws.view(torch.int64) != before).sum()) - counters, record)
+        if dtype == "fp32" and H_kv == 2:  # one range per workgroup at any size
+            assert n_parts > 64
+        else:
+            assert rest == 0 and n_parts > 256 and n_parts in (parts or n_parts,)
+            assert counters == n_parts // 32 + (n_parts % 32 > 1) + 1
         if got is None:
             got = out
             assert_parity(got, run_oracle(b), strict=False, what=f"{pages} pages")
