@@ -66,6 +66,9 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int B = a.B;
 
+  // Rows of a chunk of L from row q0 that are there: at head_dim 64 none past the
+  // call's, whatever query_start_loc says (as on the split-K kernel).
+  auto present = [&](int q0, int L) { return kF16 ? L : q0 < 0 ? 0 : min(L, a.rows - q0); };
   // items per sequence: ceil(L / PB) * H_kv for chunks (L >= min_rows: 1 where
   // no stream kernel takes the single rows), else 0; s_cum[b] = items of
   // sequences before b
@@ -74,9 +77,9 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
     const int b0 = min(B, tid * per), b1 = min(B, b0 + per);
     int local = 0;
     for (int b = b0; b < b1; ++b) {
-      const int L = a.query_start_loc[b + 1] - a.query_start_loc[b];
+      const int q0 = a.query_start_loc[b], L = a.query_start_loc[b + 1] - q0;
       s_cum[b] = local;
-      local += L >= a.min_rows ? ((L + PB - 1) / PB) * a.H_kv : 0;
+      local += L >= a.min_rows ? ((max(present(q0, L), 0) + PB - 1) / PB) * a.H_kv : 0;
     }
     const int off = block_exclusive_scan<kPfThreads>(local, s_scan);
     for (int b = b0; b < b1; ++b) s_cum[b] += off;
@@ -113,15 +116,11 @@ __device__ __forceinline__ void prefill_body(const PrefillArgs& a, PrefillSmem& 
     const int q0 = a.query_start_loc[b];
     const int L = a.query_start_loc[b + 1] - q0;
     const int C = a.context_lens[b];
-    const int nblk = (L + PB - 1) / PB;
+    const int nblk = (present(q0, L) + PB - 1) / PB;
     const int rem = f - s_cum[b];
     const int g = rem / nblk, jb = rem - g * nblk;
     const int pos0 = jb * PB;                     // first chunk position of the block
-    int npos = min(PB, L - pos0);                 // valid positions in the block
-    if constexpr (!kF16) {  // no row past the call's, whatever query_start_loc says (as on the split-K kernel)
-      npos = min(npos, a.rows - (q0 + pos0));
-      if (npos <= 0 || q0 < 0) continue;
-    }
+    const int npos = min(PB, present(q0, L) - pos0);  // valid positions in the block
     const bool bad = C > a.max_context_len || L > C || (C + kPage - 1) / kPage > (int)a.bt_stride;
 
     __syncthreads();  // previous item's readers of s_k / s_v / s_bt are done

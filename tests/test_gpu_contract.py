@@ -72,6 +72,19 @@ def test_rows_past_num_q_rows_are_not_written(cut):
     assert_parity(got[:n], run_oracle(b)[:n], strict=False, what="rows of the call")
 
 
+def test_query_start_loc_far_past_the_rows():
+    """The last entry near 2^30 (the first chunk in order, the second of which
+    one row is the call's): the work is bounded by the call's rows."""
+    announce("query_start_loc far past the rows")
+    rows = [40, 60]
+    b = _batch(rows, [70, 60], 4, 8, 64, 3)
+    dev = upload(b)
+    dev["qsl"][2] = 1 << 30
+    got = _call(b, dev, 41, 40)
+    assert_parity(got[:40], run_oracle(b)[:40], strict=False, what="rows of the first chunk")
+    assert np.isnan(got[40:]).all()  # (a chunk longer than its context, its row 40 without a key; the others not written)
+
+
 def test_chunk_longer_than_its_context():
     announce("D=64 chunk longer than its context")
     rows, ctx = [9, 20, 2], [5, 120, 1]
